@@ -9,34 +9,11 @@
 // touch the grid and the grid needs no clearing.
 #include <type_traits>
 
-#include "particles.hpp"
+#include "deposit.hpp"
 
 namespace fsest {
 
 // ------------------------------------------------------------------ deposit
-// Fixed-point accumulation.  LDS float atomics are ~20x slower than integer
-// ones on gfx950, so a workgroup sums its tile in unsigned integers: a weight
-// product w in [0, 1] adds floor(w * S + 1/2).  Two formats:
-//  * wide (64-bit): S = 2^32 - 2^8; a grid sums to N_P < 2^31 units, so no
-//    cell can overflow;
-//  * narrow (32-bit): S = 2^F with F chosen on the device from the largest
-//    bucket count M of this deposit.  A cell only receives particles whose
-//    first grid's first stencil cell lies within p + 1 cells of it per axis
-//    (at most 2 buckets per axis for p <= 4, 3 for p = 5, 6), and one
-//    particle gives a cell at most w_max^3 (w_max the largest 1D weight of
-//    the order: 1, 1, 3/4, 2/3, 115/192, 11/20), so its sum is at most
-//    K (w_max^3 S + 1/2) units with K = 8 M (27 M) possible contributors; F
-//    is the largest value keeping that below 2^32.  F >= 22 is required
-//    (24 with masses, where the unit is the largest mass), or the wide
-//    kernel runs instead (both are launched; the one not selected returns
-//    at once).  Each contribution is rounded to 2^-(F+1) <= 2^-23 of a unit
-//    mass; F < 24 only happens when the largest bucket (64 cells) holds more
-//    than 32 (NGP) to 108 (PCS) particles, where cells sum several units and
-//    float32 accumulation would round each addition at least as coarsely.
-// Integer sums are exact, so deposits are bitwise reproducible.
-constexpr float kFixWide = 4294967040.0f;  // 2^32 - 2^8
-constexpr int kNarrowMinBits = 22;
-
 // The base cells of the particles that reach one cell span p + 1 cells per
 // axis (both grids), so they meet at most 2 buckets per axis for p <= 4 and
 // 3 for p = 5, 6.
@@ -109,12 +86,6 @@ static_assert(kAccWord >= kAccMargin && kAccWordWide / 2 >= kAccMargin && kAccWo
               "base addresses stay non-negative");
 template <typename AT>
 __device__ __host__ constexpr int acc_first_word() { return sizeof(AT) == 4 ? kAccWord : kAccWordWide; }
-
-struct DepRanges {
-  uint32_t start[72];
-  uint32_t pref[73];
-  int count;
-};
 
 // Position of a stencil's first cell relative to the tile origin t0, mod N.
 // For a tile smaller than the grid the result lies in [-(P-1), n - P + 1)
@@ -214,33 +185,6 @@ __device__ __forceinline__ void deposit_item(uint4 rec, int gi, const Geom& g, i
   }
 }
 
-// Segment of each lane's candidate `item` (the wave's candidates are c0 ..
-// c0 + 63): the last t < nr with pref[t] <= item, i.e. the number of
-// starts pref[0..nr] at or below it, minus one (pref[nr] = total lies above
-// every candidate; empty pieces repeat a start and count twice, which
-// still lands on the non-empty piece).  Lane t holds starts t and t + 64:
-// one ballot counts those at or below c0 for the whole wave, and the few
-// inside the window are added lane by lane.
-__device__ __forceinline__ int find_segment(const DepRanges& rg, int nr, uint32_t c0,
-                                            uint32_t item, int lane) {
-  const uint32_t pa = lane <= nr ? rg.pref[lane] : 0xFFFFFFFFu;
-  const uint32_t pb = lane + 64 <= nr ? rg.pref[lane + 64] : 0xFFFFFFFFu;
-  int cnt = __popcll(__ballot(pa <= c0)) + __popcll(__ballot(pb <= c0));
-  unsigned long long ia = __ballot(pa > c0 && pa <= c0 + 63);
-  unsigned long long ib = __ballot(pb > c0 && pb <= c0 + 63);
-  while (ia) {
-    const int t = __builtin_ctzll(ia);
-    cnt += item >= (uint32_t)__builtin_amdgcn_readlane((int)pa, t) ? 1 : 0;
-    ia &= ia - 1;
-  }
-  while (ib) {
-    const int t = __builtin_ctzll(ib);
-    cnt += item >= (uint32_t)__builtin_amdgcn_readlane((int)pb, t) ? 1 : 0;
-    ib &= ib - 1;
-  }
-  return cnt - 1;
-}
-
 // One workgroup owns one T^3 output tile (T = min(kTileMax, N)) of every
 // grid at a time.  Per tile: (1) the particles of the buckets that can
 // reach the tile are scanned in rounds of blockDim items; each grid whose
@@ -274,10 +218,8 @@ __device__ __forceinline__ int find_segment(const DepRanges& rg, int nr, uint32_
 // a separate instantiation so that the equal-mass kernel keeps its registers
 // IL: 0 one grid; 1 the interlaced pair (masks 0 and 7); 2 a pair of grids
 // with run-time masks (mask_a, mask_b) written to slab q of each set
-// CAP: registers capped at 64 (8 waves per SIMD) so that two 1024-thread
-// workgroups share a CU (two_groups_per_cu)
-template <int P, int IL, bool WIDE, int WRAP, bool WT, bool CAP>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(CAP ? 8 : 1))) void k_deposit(const uint4* __restrict__ recs,
+template <int P, int IL, bool WIDE, int WRAP, bool WT>
+__global__ __launch_bounds__(1024) void k_deposit(const uint4* __restrict__ recs,
                                                   const uint32_t* __restrict__ boff,
                                                   const uint32_t* __restrict__ bcnt, float* grid,
                                                   Geom g, uint32_t* __restrict__ stats,
@@ -303,7 +245,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(CAP ? 8 : 
   // computed it from the sort's largest bucket count)
   const int nbits = (int)stats[6];
   // with masses the step is relative to the largest mass: F >= 24 there
-  constexpr int kMinBits = WT ? 24 : kNarrowMinBits;
+  constexpr int kMinBits = WT ? kNarrowMinBitsMass : kNarrowMinBits;
   if (!WIDE && nbits < kMinBits) return;                // the wide kernel does it
   if (WIDE && !exclusive && nbits >= kMinBits) return;  // the narrow one does it
   const float scale = WIDE ? kFixWide : ldexpf(1.0f, nbits);
@@ -500,9 +442,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(CAP ? 8 : 
       int rpar = 0;  // which of the three round counters this round uses
 
       // rounds of blockDim candidates; the cell records of kPre rounds are
-      // loaded together so that their latencies overlap (one round where the
-      // registers are capped: the other workgroup on the CU covers the wait)
-      constexpr int kPre = CAP ? 1 : 4;
+      // loaded together so that their latencies overlap
+      constexpr int kPre = 4;
       constexpr int off = (P % 2 == 0) ? (P / 2 - 1) : (P - 1) / 2;
       for (uint32_t rb = 0; rb < total; rb += kPre * nthreads) {
         uint32_t jj[kPre];
@@ -684,22 +625,6 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(CAP ? 8 : 
   }
 }
 
-// A workgroup waits at a barrier several times per tile, and with one
-// workgroup per CU the whole CU waits with it.  The 32-bit pair kernel's LDS
-// (74.9 KB) leaves room for two workgroups per CU; those of 1024 threads need
-// 8 waves per SIMD, i.e. at most 64 VGPRs.  The instantiations listed here
-// fit in 64 without scratch (the others spill and keep their registers):
-// the interlaced pair, float32 positions, equal masses, orders 1 and 2, and
-// order 4 with a tile smaller than the grid.  Measured at 1024^3 with 2^27
-// particles (PCS): 11.8 ms with two 512-thread workgroups per CU, 10.8 ms
-// with two of 1024.
-template <int P, int IL, bool WIDE, int WRAP, bool WT>
-__host__ __device__ constexpr bool two_groups_per_cu() {
-  return !WIDE && IL == 1 && !WT && (P <= 2 || (P == 4 && WRAP != kPeriodic));
-}
-
-// threads: 256, 512 or 1024 per deposit workgroup, or 0 for the kernel's
-// own choice (1024 where two_groups_per_cu, else 512)
 // Segment length of the z walk: the longest of 8, 4, 2 tiles that still
 // gives every workgroup of the persistent grid about 8 units (the units of a
 // batch of uneven sets differ in cost).
@@ -721,33 +646,21 @@ static void deposit_launch(const Geom& g, const Buffers& b, int threads, bool na
   const bool walk = WRAP != kPeriodic && g.n >= g.tile + kBucket * kLow;
   const int seg = walk ? walk_segment(g, cus) : 1;
   const int64_t nunits = (int64_t)g.batch * tpa * tpa * ((tpa + seg - 1) / seg);
-  constexpr bool kTwo = two_groups_per_cu<P, IL, false, WRAP, WT>();
   if (narrow) {
-    const int tn = threads ? threads : (kTwo ? 1024 : 512);
     // a persistent grid: 8 workgroups per CU (a multiple of 8 for the XCD
     // grouping), each looping over units
     const int64_t cap = (int64_t)cus * 8;
     const unsigned nwg = (unsigned)(nunits < cap ? nunits : cap);
-    bool capped = false;
-    if constexpr (kTwo) {
-      if (tn == 1024) {
-        hipLaunchKernelGGL((k_deposit<P, IL, false, WRAP, WT, true>), dim3(nwg), dim3(tn), 0, s,
-                           (const uint4*)b.recs, b.boff, b.bcnt, (float*)b.grid, g, b.stats, 0, 0,
-                           xcd ? 1 : 0, sw, q, ma, mb, walk ? 1 : 0, seg);
-        capped = true;
-      }
-    }
-    if (!capped)
-      hipLaunchKernelGGL((k_deposit<P, IL, false, WRAP, WT, false>), dim3(nwg), dim3(tn), 0, s,
-                         (const uint4*)b.recs, b.boff, b.bcnt, (float*)b.grid, g, b.stats, 0, 0,
-                         xcd ? 1 : 0, sw, q, ma, mb, walk ? 1 : 0, seg);
+    hipLaunchKernelGGL((k_deposit<P, IL, false, WRAP, WT>), dim3(nwg), dim3(threads), 0, s,
+                       (const uint4*)b.recs, b.boff, b.bcnt, (float*)b.grid, g, b.stats, 0, 0,
+                       xcd ? 1 : 0, sw, q, ma, mb, walk ? 1 : 0, seg);
   }
   // the 64-bit kernel holds one workgroup per CU; it takes units from a
   // counter, so when the 32-bit kernel does the work it costs one short wave
   // per workgroup
   const unsigned wblocks = (unsigned)(nunits < 1024 ? nunits : 1024);
-  hipLaunchKernelGGL((k_deposit<P, IL, true, WRAP, WT, false>), dim3(wblocks),
-                     dim3(threads ? threads : 512), 0, s, (const uint4*)b.recs, b.boff, b.bcnt,
+  hipLaunchKernelGGL((k_deposit<P, IL, true, WRAP, WT>), dim3(wblocks),
+                     dim3(threads), 0, s, (const uint4*)b.recs, b.boff, b.bcnt,
                      (float*)b.grid, g, b.stats, narrow ? 0 : 1, 1, 0, sw, q, ma, mb,
                      walk ? 1 : 0, seg);
 }
@@ -764,12 +677,19 @@ static void dispatch_deposit_t(const Geom& g, const Buffers& b, const Tune& tu, 
                                const float* sw, int q, int ma, int mb, hipStream_t s) {
   const bool narrow = tu.dep_narrow != 0;
   const bool xcd = tu.dep_xcd != 0;
-  if (g.tile == g.n)
+  if (g.tile == g.n) {
     dispatch_deposit_w<P, IL, kPeriodic>(g, b, threads, narrow, xcd, tu.cus, sw, q, ma, mb, s);
-  else if ((g.n & (g.n - 1)) == 0)
+    return;
+  }
+  // orders 1..4 on larger grids walk smaller tiles with lighter work items:
+  // at 1024^3 with 2^27 particles (PCS pair) 5.73 ms against 6.41 ms here
+  if constexpr (P <= 4) {
+    (void)launch_deposit_walk(g, b, tu, sw, q, ma, mb, s);  // reported by launch_deposit
+  } else if ((g.n & (g.n - 1)) == 0) {
     dispatch_deposit_w<P, IL, kMasked>(g, b, threads, narrow, xcd, tu.cus, sw, q, ma, mb, s);
-  else
+  } else {
     dispatch_deposit_w<P, IL, kGeneral>(g, b, threads, narrow, xcd, tu.cus, sw, q, ma, mb, s);
+  }
 }
 
 template <int P>
@@ -792,8 +712,7 @@ static void dispatch_deposit_p(const Geom& g, const Buffers& b, const Tune& tu, 
 
 hipError_t launch_deposit(const Geom& g, const Buffers& b, const Tune& tu, bool weighted,
                           hipStream_t s) {
-  int threads = tu.dep_threads;
-  if (threads != 256 && threads != 512 && threads != 1024) threads = 0;  // per kernel
+  const int threads = tu.dep_threads == 1024 ? 1024 : 512;
   const float* sw = weighted ? b.sw : nullptr;
   switch (g.order) {
     case 1: dispatch_deposit_p<1>(g, b, tu, threads, sw, s); break;
