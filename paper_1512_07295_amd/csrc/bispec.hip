@@ -25,8 +25,10 @@
 //     f32 16x16x4 instructions evaluate on tiles of 16 consecutive b2 by 16
 //     consecutive b3 ("jobs"; 996 jobs cover the 185,056 closed triangles of
 //     128 shells).  A workgroup stages 64-point chunks of every field in LDS
-//     and each wave keeps 16 jobs' accumulators in registers: FP32 products
-//     and sums over a chunk, FP64 across chunks;
+//     and each wave keeps up to 16 jobs' accumulators in registers: FP32
+//     products and sums over a chunk, FP64 across chunks.  The jobs are split
+//     evenly over the waves: with the first waves full and the others idle,
+//     32 shells on 200^3 (35 jobs) took 0.46 ms per slab, now 0.19;
 //  5. per-workgroup sums are reduced in a fixed order, slab after slab.
 // The J sums depend only on (M, n_dk, n_bins, the jobs) and are cached by the
 // caller (api.hip) after the first call.
@@ -44,7 +46,10 @@ constexpr int kBsMaxS = 32;          // x planes per slab, at most
 constexpr int kBsWaves = 8;          // waves of a triple-sum workgroup
 constexpr int kBsJobsPerWave = 16;   // 16x16 tiles whose accumulators a wave holds
 constexpr int kBsJobsPerGroup = kBsWaves * kBsJobsPerWave;
-constexpr int kBsTargetBlocks = 1024;  // triple-sum workgroups per slab, about
+// triple-sum workgroups per slab, about: two rounds over the CUs (one
+// workgroup each, by its registers); more only add partial sums to write and
+// reduce (32 shells on 200^3: 1024 ranges took 0.26 ms per slab to reduce)
+constexpr int kBsTargetBlocks = 512;
 constexpr size_t kBsSlabBudget = (size_t)8 << 30;  // bytes of one slab's fields, at most
 
 // ------------------------------------------------------------------ plan (host)
@@ -149,7 +154,7 @@ __global__ void k_bs_twiddles(int M, float2* tw) {
 }
 
 // delta(m) = C(m) / (N_P W(m)) for |m_a| <= R inside shells 1..n_bins (zero
-// elsewhere and at m = 0), cube index ((m_z + R) W + m_y + R) W + m_x + R
+// elsewhere and at m = 0), cube index ((m_x + R) W + m_y + R) W + m_z + R
 __global__ __launch_bounds__(256) void k_bs_band(const float2* __restrict__ data, Geom g, int mock,
                                                  int R, int n_dk, int n_bins,
                                                  const float2* __restrict__ phase,
@@ -161,7 +166,7 @@ __global__ __launch_bounds__(256) void k_bs_band(const float2* __restrict__ data
   const float inv_np = 1.0f / (float)norm[2 * mock];
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * blockDim.x) {
-    const int mx = (int)(e % W) - R, my = (int)((e / W) % W) - R, mz = (int)(e / ((int64_t)W * W)) - R;
+    const int mz = (int)(e % W) - R, my = (int)((e / W) % W) - R, mx = (int)(e / ((int64_t)W * W)) - R;
     const int m2 = mx * mx + my * my + mz * mz;
     const int b = m2 ? shell_of(m2, n_dk) : 0;
     float2 d = make_float2(0.f, 0.f);
@@ -198,6 +203,12 @@ __device__ __forceinline__ int isqrt_floor(int v) {
 // b1 = 2q+1, b2 = 2q+2 (if <= n_bins), d = delta (or 1 for the counts), at
 // slab index ((q S + x - x0) M + (m_y mod M)) M + (m_z mod M); zero outside
 // |m_y|, |m_z| <= R.  One thread per (q, m_y index, m_z index).
+// Bound by the twiddle reads and the divergence of the m_x ranges; 32 shells
+// on 200^3 (131^3 modes, 25 planes): 145 us per slab with a wait per plane and
+// one sign of m_x at a time, 78 us now, 25 us to write the slab.
+// NS >= S planes are summed (a compile-time count, so that the LDS reads of a
+// mode's twiddles are in flight together; the ones past S are not stored).
+template <int NS>
 __global__ __launch_bounds__(256) void k_bs_xdft(const float2* __restrict__ band, int R, int M,
                                                  int S, int x0, int Q, int n_dk, int n_bins,
                                                  int counts, const float2* __restrict__ twm,
@@ -209,9 +220,9 @@ __global__ __launch_bounds__(256) void k_bs_xdft(const float2* __restrict__ band
   if (tid >= (int64_t)Q * M * M) return;
   const int bz = (int)(tid % M), ay = (int)((tid / M) % M), q = (int)(tid / ((int64_t)M * M));
   const int my = ay <= M / 2 ? ay : ay - M, mz = bz <= M / 2 ? bz : bz - M;
-  float2 acc[kBsMaxS];
+  float2 acc[NS];
 #pragma unroll
-  for (int xl = 0; xl < kBsMaxS; ++xl) acc[xl] = make_float2(0.f, 0.f);
+  for (int xl = 0; xl < NS; ++xl) acc[xl] = make_float2(0.f, 0.f);
   if (my >= -R && my <= R && mz >= -R && mz <= R) {
     const int b1 = 2 * q + 1, bhi = (2 * q + 2 <= n_bins) ? 2 * q + 2 : b1;
     const int W = 2 * R + 1;
@@ -225,36 +236,40 @@ __global__ __launch_bounds__(256) void k_bs_xdft(const float2* __restrict__ band
       int umin = lo4 <= 0 ? 0 : isqrt_floor((lo4 + 3) / 4) - 1;
       if (umax > R) umax = R;
       if (umin < 0) umin = 0;
-      const float2* row = band + ((int64_t)(mz + R) * W + (my + R)) * W + R;
+      // neighbouring threads (m_z) read neighbouring elements for each m_x
+      const float2* col = band + ((int64_t)R * W + (my + R)) * W + (mz + R);
+      const int64_t xstep = (int64_t)W * W;
       for (int u = umin; u <= umax; ++u) {
         const int m2 = u * u + rho2;
         if (m2 == 0) continue;
         const int b = shell_of(m2, n_dk);
         if (b != b1 && b != bhi) continue;
-        for (int sg = 0; sg < 2; ++sg) {
-          if (u == 0 && sg == 1) continue;
-          const int mx = sg ? -u : u;
-          float2 d = counts ? make_float2(1.f, 0.f) : row[mx];
-          if (b != b1) d = make_float2(-d.y, d.x);  // i d: the imaginary field
-          const int step = mx >= 0 ? mx : mx + M;
-          int idx = (int)(((int64_t)step * x0) % M);
+        float2 d = counts ? make_float2(1.f, 0.f) : col[u * xstep];
+        float2 e = counts ? make_float2(1.f, 0.f) : col[-u * xstep];
+        if (u == 0) e = make_float2(0.f, 0.f);  // m_x = 0 once
+        if (b != b1) {  // times i: the imaginary field
+          d = make_float2(-d.y, d.x);
+          e = make_float2(-e.y, e.x);
+        }
+        // m_x = u and -u share their twiddles: those of -u are the conjugates
+        const uint32_t step = (uint32_t)u * sizeof(float2), wrap = (uint32_t)M * sizeof(float2);
+        uint32_t at = (uint32_t)(((int64_t)u * x0) % M) * sizeof(float2);
 #pragma unroll
-          for (int xl = 0; xl < kBsMaxS; ++xl) {
-            if (xl < S) {
-              const float2 w = tw[idx];  // exp(-2 pi i idx / M); conjugated below
-              acc[xl].x += d.x * w.x + d.y * w.y;
-              acc[xl].y += d.y * w.x - d.x * w.y;
-              idx += step;
-              if (idx >= M) idx -= M;
-            }
-          }
+        for (int xl = 0; xl < NS; ++xl) {
+          const float2 w = *(const float2*)((const char*)tw + at);  // exp(-2 pi i u x / M)
+          acc[xl].x += d.x * w.x + d.y * w.y;
+          acc[xl].y += d.y * w.x - d.x * w.y;
+          acc[xl].x += e.x * w.x - e.y * w.y;
+          acc[xl].y += e.y * w.x + e.x * w.y;
+          at += step;
+          at = min(at, at - wrap);  // mod M: at - wrap is huge below it
         }
       }
     }
   }
   float2* out = slab + ((int64_t)q * S * M + ay) * M + bz;
 #pragma unroll
-  for (int xl = 0; xl < kBsMaxS; ++xl)
+  for (int xl = 0; xl < NS; ++xl)
     if (xl < S) out[(int64_t)xl * M * M] = acc[xl];
 }
 
@@ -263,12 +278,12 @@ __global__ __launch_bounds__(256) void k_bs_xdft(const float2* __restrict__ band
 // (d, r0, c0) is the 16x16 tile T(i, j) = sum_p I_b1 I_b2 I_b3 with
 // b2 = bs + 16 r0 + i, b1 = b2 + d, b3 = bs + 16 c0 + j, bs = max(d, 1)
 // (shells above n_bins read a zero row).  Workgroup = (point range, job
-// group); wave w of the group owns jobs g 128 + 16 w .. + 15.  MFMA
+// group); the jobs are split evenly over the groups' waves.  MFMA
 // v_mfma_f32_16x16x4f32: lane l supplies A[l % 16][l / 16] and
 // B[l / 16][l % 16] and holds D[4 (l / 16) + r][l % 16] in register r; lane
 // l's four K-slots of the PC/4 steps are the points (l / 16) PC/4 + s.
-template <int PC>
-__global__ __launch_bounds__(kBsWaves * 64) void k_bs_triple(
+template <int PC, int JPW>
+__global__ __launch_bounds__(kBsWaves * 64, JPW <= 8 ? 4 : 2) void k_bs_triple(
     const float2* __restrict__ slab, int64_t npts, int Q, int n_bins,
     const int32_t* __restrict__ jobs, int njobs, int ngroups, int nranges,
     double* __restrict__ partial) {
@@ -279,11 +294,13 @@ __global__ __launch_bounds__(kBsWaves * 64) void k_bs_triple(
   const int grp = blockIdx.x % ngroups, rng = blockIdx.x / ngroups;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, i16 = lane & 15, k4 = lane >> 4;
-  const int j0 = grp * kBsJobsPerGroup + wave * kBsJobsPerWave;
-  const int nj = njobs - j0 < 0 ? 0 : (njobs - j0 > kBsJobsPerWave ? kBsJobsPerWave : njobs - j0);
-  double acc[kBsJobsPerWave][4];
+  // the jobs are split evenly over the groups and each group's over its waves
+  const int gj0 = (int)((int64_t)njobs * grp / ngroups), gj1 = (int)((int64_t)njobs * (grp + 1) / ngroups);
+  const int j0 = gj0 + (gj1 - gj0) * wave / kBsWaves;
+  const int nj = gj0 + (gj1 - gj0) * (wave + 1) / kBsWaves - j0;  // <= JPW
+  double acc[JPW][4];
 #pragma unroll
-  for (int jj = 0; jj < kBsJobsPerWave; ++jj)
+  for (int jj = 0; jj < JPW; ++jj)
 #pragma unroll
     for (int r = 0; r < 4; ++r) acc[jj][r] = 0.0;
 
@@ -292,7 +309,8 @@ __global__ __launch_bounds__(kBsWaves * 64) void k_bs_triple(
   // the zero row (shells above n_bins)
   for (int t = threadIdx.x; t < STRIDE; t += NT) fld[n_bins * STRIDE + t] = 0.0f;
   // this thread's share of a chunk: elements e = threadIdx.x + NT u of Q x PC
-  constexpr int UMAX = (128 * 32 + NT - 1) / NT;  // Q PC <= 4096 by the choice of PC
+  // Q PC <= 4096 by the choice of PC, <= 2048 for the small variant
+  constexpr int UMAX = (JPW <= 8 ? 2048 : 4096) / NT;
   const int nel = Q * PC;
   float2 pre[UMAX];
   auto fetch = [&](int64_t c) __attribute__((always_inline)) {
@@ -324,7 +342,7 @@ __global__ __launch_bounds__(kBsWaves * 64) void k_bs_triple(
     float a[KS], bv[KS];
     int prev_d = -1, prev_r0 = -1;
 #pragma unroll
-    for (int jj = 0; jj < kBsJobsPerWave; ++jj) {
+    for (int jj = 0; jj < JPW; ++jj) {
       if (jj < nj) {
         // job descriptor (wave-uniform: scalar loads); LDS rows of the A
         // factors (b1, b2) and the B factor (b3) of this lane's row / column,
@@ -368,7 +386,7 @@ __global__ __launch_bounds__(kBsWaves * 64) void k_bs_triple(
     }
   }
 #pragma unroll
-  for (int jj = 0; jj < kBsJobsPerWave; ++jj) {
+  for (int jj = 0; jj < JPW; ++jj) {
     if (jj < nj) {
       double* dst = partial + ((int64_t)rng * njobs + j0 + jj) * 256;
 #pragma unroll
@@ -377,13 +395,27 @@ __global__ __launch_bounds__(kBsWaves * 64) void k_bs_triple(
   }
 }
 
-// run[j] += sum over point ranges of partial[range][j], ranges in order
-__global__ void k_bs_reduce(const double* __restrict__ partial, int64_t entries, int nranges,
-                            double* __restrict__ run) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= entries) return;
+// run[j] += sum over point ranges of partial[range][j]: a workgroup takes 64
+// entries, its 16 waves a sixteenth of the ranges each, the sixteenths added
+// in order
+constexpr int kBsReduceWaves = 16;
+
+__global__ __launch_bounds__(kBsReduceWaves * 64) void k_bs_reduce(const double* __restrict__ partial,
+                                                                   int64_t entries, int nranges,
+                                                                   double* __restrict__ run) {
+  __shared__ double part[kBsReduceWaves][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t e = (int64_t)blockIdx.x * 64 + lane;
   double s = 0.0;
-  for (int r = 0; r < nranges; ++r) s += partial[(int64_t)r * entries + e];
+  if (e < entries) {
+    const int r1 = nranges * (wave + 1) / kBsReduceWaves;
+#pragma unroll 4
+    for (int r = nranges * wave / kBsReduceWaves; r < r1; ++r) s += partial[(int64_t)r * entries + e];
+  }
+  part[wave][lane] = s;
+  __syncthreads();
+  if (wave != 0 || e >= entries) return;
+  for (int w = 1; w < kBsReduceWaves; ++w) s += part[w][lane];
   run[e] += s;
 }
 
@@ -413,17 +445,17 @@ hipError_t launch_bs_setup(const Geom& g, const Buffers& b, int mock, int n_dk, 
   return hipGetLastError();
 }
 
-template <int PC>
+template <int PC, int JPW>
 static hipError_t triple_t(const BsPlan& pl, const float2* slab, int n_bins, const int32_t* jobs,
                            double* part, hipStream_t s) {
   const size_t lds = sizeof(float) * (size_t)(n_bins + 1) * (PC + 4);
   static bool attr = false;
   if (!attr) {
-    (void)hipFuncSetAttribute((const void*)k_bs_triple<PC>,
+    (void)hipFuncSetAttribute((const void*)k_bs_triple<PC, JPW>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     attr = true;
   }
-  hipLaunchKernelGGL((k_bs_triple<PC>), dim3((unsigned)(pl.ngroups * pl.nranges)),
+  hipLaunchKernelGGL((k_bs_triple<PC, JPW>), dim3((unsigned)(pl.ngroups * pl.nranges)),
                      dim3(kBsWaves * 64), lds, s, slab, pl.npts, pl.Q, n_bins, jobs, (int)pl.njobs,
                      pl.ngroups, pl.nranges, part);
   return hipGetLastError();
@@ -437,8 +469,13 @@ hipError_t launch_bs_fields(int n_dk, int n_bins, const BsPlan& pl, char* bws, b
   const int M = pl.M, R = pl.R;
   const int64_t plane = (int64_t)M * M;
   const int64_t xthreads = (int64_t)pl.Q * plane;
-  hipLaunchKernelGGL(k_bs_xdft, dim3((unsigned)((xthreads + 255) / 256)), dim3(256), 0, s, band, R, M,
-                     pl.S, slab_index * pl.S, pl.Q, n_dk, n_bins, counts ? 1 : 0, tw, slab);
+#define FSEST_XDFT(NS)                                                                              \
+  else if (pl.S <= NS)                                                                              \
+    hipLaunchKernelGGL(k_bs_xdft<NS>, dim3((unsigned)((xthreads + 255) / 256)), dim3(256), 0, s, band, \
+                       R, M, pl.S, slab_index * pl.S, pl.Q, n_dk, n_bins, counts ? 1 : 0, tw, slab);
+  if (pl.S > kBsMaxS) return hipErrorInvalidValue;
+  FSEST_XDFT(4) FSEST_XDFT(8) FSEST_XDFT(12) FSEST_XDFT(16) FSEST_XDFT(20) FSEST_XDFT(25) FSEST_XDFT(32)
+#undef FSEST_XDFT
   // inverse z transforms of the rows that carry data (|m_y| <= R), then y
   const int64_t planes = (int64_t)pl.Q * pl.S;
   hipError_t e = launch_fft_rows_len(M, slab, planes * (R + 1), R + 1, plane, +1, tw, s);
@@ -459,12 +496,15 @@ hipError_t launch_bs_triple(int n_bins, const BsPlan& pl, char* bws, bool first_
   hipError_t e = hipSuccess;
   if (first_slab && (e = launch_fill_u32((uint32_t*)run, (size_t)entries * 2, 0u, s)) != hipSuccess)
     return e;
-  if (pl.pc == 64) e = triple_t<64>(pl, slab, n_bins, jobs, part, s);
-  else if (pl.pc == 32) e = triple_t<32>(pl, slab, n_bins, jobs, part, s);
-  else e = triple_t<16>(pl, slab, n_bins, jobs, part, s);
+  // few jobs (up to about 40 shells): half the accumulators per wave, so that
+  // two workgroups share a CU
+  if (pl.pc == 64 && pl.njobs <= 8 * kBsWaves && pl.Q <= 32) e = triple_t<64, 8>(pl, slab, n_bins, jobs, part, s);
+  else if (pl.pc == 64) e = triple_t<64, 16>(pl, slab, n_bins, jobs, part, s);
+  else if (pl.pc == 32) e = triple_t<32, 16>(pl, slab, n_bins, jobs, part, s);
+  else e = triple_t<16, 16>(pl, slab, n_bins, jobs, part, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_bs_reduce, dim3((unsigned)((entries + 255) / 256)), dim3(256), 0, s, part,
-                     entries, pl.nranges, run);
+  hipLaunchKernelGGL(k_bs_reduce, dim3((unsigned)((entries + 63) / 64)), dim3(kBsReduceWaves * 64), 0, s,
+                     part, entries, pl.nranges, run);
   return hipGetLastError();
 }
 
