@@ -170,20 +170,27 @@ Geom make_geom(const est_config& c) {
   g.batch = c.batch;
   g.nb = c.n_grid / kBucket;
   // Super-bucket edge fb: a divisor of nb up to kFineMax, so super-buckets
-  // tile the axis, and at least 5 unless it is nb itself, so that a deposit
-  // run of up to 6 buckets in z meets at most one super-bucket edge (nb has
-  // no prime factor above 5, so such a divisor exists when nb > kFineMax).
+  // tile the axis, and long enough that a deposit run in z meets at most one
+  // super-bucket edge: 2 for the runs of up to 3 buckets of the z-walking
+  // deposit, 5 (or nb itself) for the 6 of the general one (nb has no prime
+  // factor above 5, so such a divisor exists when nb > kFineMax).
   // Of these, the smallest whose super-bucket count batch (nb/fb)^3 stays at
-  // or below max_particles / 16384: about 16K particles per super-bucket,
-  // enough per (workgroup chunk, super-bucket) for whole-line writes in the
-  // super-bucket pass, and as many super-buckets as that allows for the
-  // bucket pass, which runs one workgroup per super-bucket (many uneven sets
-  // then spread over the chip).  If none qualifies, the largest.
+  // or below max_particles / 4096, so that the bucket pass scatters inside
+  // 64 KB and many uneven super-buckets spread over the chip (512^3 clustered
+  // CIC: sort 0.83 ms with 16K particles per super-bucket, 0.79 with 4K; 256^3
+  // in lattice order 0.343 and 0.331, in random order 0.702 and 0.730), but at
+  // small sizes below max_particles / 512, up to 512 super-buckets, so that
+  // the bucket pass has workgroups (32768 particles on 64^3: sort 61 us with
+  // two super-buckets, 25 with 64).  If none qualifies, the largest.
   {
-    const int64_t target = c.max_particles / 16384 > 1 ? c.max_particles / 16384 : 1;
+    const int least = c.order <= 4 && c.n_grid > kTileMax ? 2 : 5;
+    int64_t target = c.max_particles / 512 < 512 ? c.max_particles / 512 : 512;
+    if (target < c.max_particles / 4096) target = c.max_particles / 4096;
+    if (target < 1) target = 1;
+    if (target > kMaxSuper) target = kMaxSuper;
     int small_ok = 0, largest = 0;
     for (int d = 1; d <= kFineMax && d <= g.nb; ++d) {
-      if (g.nb % d != 0 || (d < 5 && d != g.nb)) continue;
+      if (g.nb % d != 0 || (d < least && d != g.nb)) continue;
       largest = d;
       const int64_t sa = g.nb / d;
       if (!small_ok && (int64_t)c.batch * sa * sa * sa <= target) small_ok = d;
@@ -222,8 +229,8 @@ size_t layout(const est_config& c, char* base, Buffers* b, void** tune_out) {
   bb.bcnt = (uint32_t*)take(nkeys * sizeof(uint32_t));
   const bool two_level = g.nsup <= kMaxSuper;
   bb.trecs = two_level ? (uint4*)take((size_t)c.max_particles * sizeof(uint4)) : nullptr;
-  // block-major histograms (kMaxSortBlocks rows of nsup) and the nsup + 1 super-bucket starts
-  const size_t nh = two_level ? (size_t)g.nsup * kMaxSortBlocks + g.nsup + 1 : 0;
+  // block-major histograms (kMaxSortBlocks rows of nsup), the nsup + 1 super-bucket starts, nsup totals
+  const size_t nh = two_level ? (size_t)g.nsup * (kMaxSortBlocks + 2) + 1 : 0;
   bb.hsup = two_level ? (uint32_t*)take(nh * sizeof(uint32_t)) : nullptr;
   const size_t nscan = nkeys > nh ? nkeys : nh;
   bb.scan_tmp = (uint32_t*)take(((nscan + 2047) / 2048 + 1) * sizeof(uint32_t));
@@ -241,7 +248,7 @@ size_t layout(const est_config& c, char* base, Buffers* b, void** tune_out) {
   const bool weighted = (c.flags & EST_FLAG_WEIGHTS) != 0;
   bb.sw = weighted ? (float*)take((size_t)c.max_particles * sizeof(float)) : nullptr;
   bb.tw = weighted && two_level ? (float*)take((size_t)c.max_particles * sizeof(float)) : nullptr;
-  bb.wpart = weighted ? (double*)take(batch * weight_slices(c.batch) * 2 * sizeof(double)) : nullptr;
+  bb.wpart = weighted ? (double*)take(batch * weight_slices(c.batch) * kWPartDoubles * sizeof(double)) : nullptr;
   bb.cbuf = c.interlace >= 2 ? (float2*)take(batch * n * n * (half + 1) * sizeof(float2)) : nullptr;
   bb.coef = (double*)take(batch * half * sizeof(double));
   bb.mode_partials_n = (uint64_t*)take(512 * half * sizeof(uint64_t));
@@ -303,15 +310,6 @@ est_status run_deposit(est_handle h, const void* pos, est_dtype dt, const int64_
   est_status st;
   {
     ProfScope ps(h, kPSort);
-    st = dev_err(launch_set_counts(offsets, n_total, h->g.batch, h->b.np, h->b.norm, h->stream),
-                 "counts");
-    if (st) return st;
-    if (h->weights) {
-      st = dev_err(launch_weight_stats(h->weights, offsets, n_total, h->g.batch, h->b.wpart,
-                                       h->b.norm, h->b.stats, h->stream),
-                   "mass sums");
-      if (st) return st;
-    }
     st = dev_err(launch_sort(h->g, pos, dt, offsets, n_total, h->weights, h->b, h->stream),
                  "bucket sort");
     if (st) return st;

@@ -14,27 +14,6 @@
 namespace fsest {
 
 // ------------------------------------------------------------------ deposit
-// The base cells of the particles that reach one cell span p + 1 cells per
-// axis (both grids), so they meet at most 2 buckets per axis for p <= 4 and
-// 3 for p = 5, 6.
-template <int P>
-__device__ __forceinline__ int narrow_bits(uint32_t maxcount) {
-  // w_max^3 of the order, with a margin for the float32 rounding of the
-  // weight products
-  constexpr double wmax = P <= 2 ? 1.0 : (P == 3 ? 0.75 : (P == 4 ? 2.0 / 3.0 : (P == 5 ? 115.0 / 192.0 : 0.55)));
-  constexpr double w3 = wmax * wmax * wmax * (1.0 + 1e-6);
-  const double k = (P <= 4 ? 8.0 : 27.0) * (double)(maxcount > 0 ? maxcount : 1);
-  int f = 0;
-  while (f < 31 && k * (w3 * ldexp(1.0, f + 1) + 0.5) < 4294967295.0) ++f;
-  return f;
-}
-
-// The 32-bit format's fraction bits for this deposit, once per deposit.
-template <int P>
-__global__ void k_narrow(uint32_t* stats) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) stats[6] = (uint32_t)narrow_bits<P>(stats[0]);
-}
-
 // LDS layout of a deposit workgroup, in 32-bit words:
 //   [0, kItemCap)            particle index of each work item
 //   [.., + kItemCap/4)       item meta bytes: bank class (6 bits) | grid << 6
@@ -241,9 +220,8 @@ __global__ __launch_bounds__(1024) void k_deposit(const uint4* __restrict__ recs
   AT* sm = reinterpret_cast<AT*>(smem);
   const int acc0 = acc_first_word<AT>() * 4 / (int)sizeof(AT);
 
-  // fixed-point format for this deposit (uniform over the grid; k_narrow
-  // computed it from the sort's largest bucket count)
-  const int nbits = (int)stats[6];
+  // fixed-point format for this deposit (uniform over the grid)
+  const int nbits = __builtin_amdgcn_readfirstlane(narrow_bits<P>(stats[0]));
   // with masses the step is relative to the largest mass: F >= 24 there
   constexpr int kMinBits = WT ? kNarrowMinBitsMass : kNarrowMinBits;
   if (!WIDE && nbits < kMinBits) return;                // the wide kernel does it
@@ -695,7 +673,6 @@ static void dispatch_deposit_t(const Geom& g, const Buffers& b, const Tune& tu, 
 template <int P>
 static void dispatch_deposit_p(const Geom& g, const Buffers& b, const Tune& tu, int threads,
                                const float* sw, hipStream_t s) {
-  hipLaunchKernelGGL(k_narrow<P>, dim3(1), dim3(64), 0, s, b.stats);
   if (g.code == 0) {
     dispatch_deposit_t<P, 0>(g, b, tu, threads, sw, 0, 0, 0, s);
   } else if (g.code == 1) {

@@ -32,6 +32,27 @@ constexpr float kFixWide = 4294967040.0f;  // 2^32 - 2^8
 constexpr int kNarrowMinBits = 22;
 constexpr int kNarrowMinBitsMass = 24;
 
+// The narrow format's fraction bits for a largest bucket count: the largest F
+// with K (w_max^3 2^F + 1/2) < 2^32 - 1, found from the logarithm and settled
+// by the condition itself.  Every workgroup computes it (a kernel of its own
+// for it cost 4 us per deposit).
+template <int P>
+__device__ __forceinline__ int narrow_bits(uint32_t maxcount) {
+  // w_max^3 of the order, with a margin for the float32 rounding of the
+  // weight products; the base cells of the particles that reach one cell span
+  // p + 1 cells per axis (both grids), so they meet at most 2 buckets per axis
+  // for p <= 4 and 3 for p = 5, 6
+  constexpr double wmax = P <= 2 ? 1.0 : (P == 3 ? 0.75 : (P == 4 ? 2.0 / 3.0 : (P == 5 ? 115.0 / 192.0 : 0.55)));
+  constexpr double w3 = wmax * wmax * wmax * (1.0 + 1e-6);
+  const double k = (P <= 4 ? 8.0 : 27.0) * (double)(maxcount > 0 ? maxcount : 1);
+  auto fits = [&](int f) { return k * (w3 * ldexp(1.0, f) + 0.5) < 4294967295.0; };
+  int f = (int)(32.0f - __log2f((float)(k * w3)));
+  f = f < 0 ? 0 : (f > 31 ? 31 : f);
+  while (f > 0 && !fits(f)) --f;
+  while (f < 31 && fits(f + 1)) ++f;
+  return f;
+}
+
 // ------------------------------------------------------------------ runs
 // A tile's candidates: runs of bucket-ordered records, run t holding the
 // candidates pref[t] .. pref[t + 1] - 1 from record start[t] on.

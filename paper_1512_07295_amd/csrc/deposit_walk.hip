@@ -104,7 +104,7 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(WI
   __shared__ int cls_cnt[2][64];
   __shared__ uint32_t unit_ring[4];      // units by their order in this workgroup (o mod 4)
 
-  const int nbits = (int)stats[6];
+  const int nbits = __builtin_amdgcn_readfirstlane(narrow_bits<P>(stats[0]));
   constexpr int kMinBits = WT ? kNarrowMinBitsMass : kNarrowMinBits;
   if (!WIDE && nbits < kMinBits) return;                // the wide kernel does it
   if (WIDE && !exclusive && nbits >= kMinBits) return;  // the narrow one does it
@@ -494,9 +494,10 @@ constexpr int walk_groups_per_cu() {
 
 // Segment length of the z walk in tiles: of 1..16 the one with the smallest
 // rounds of units over the resident workgroups times their length, half a
-// tile added per unit for its look-back.  256^3 (768 workgroups of the
-// pair): 11, one unit each, 0.60 ms against 0.64 with 4 tiles per unit;
-// large grids: 10 to 16, so that uneven units balance over many rounds.
+// tile added per unit for its look-back, and three quarters of a unit for
+// the uneven end when there are several rounds.  256^3 (768 workgroups of
+// the pair): 11 tiles, one unit each, 0.60 ms against 0.64 with 4 tiles per
+// unit; 64 uneven clustered sets of 128^3: 8 tiles, 5.1 ms against 5.6 with 16.
 static int walk_segment(const Geom& g, int64_t slots) {
   const int tpa = (g.n + kWalkT - 1) / kWalkT, tpz = (g.n + kWalkTZ - 1) / kWalkTZ;
   const int64_t cols = (int64_t)g.batch * tpa * tpa;
@@ -504,7 +505,8 @@ static int walk_segment(const Geom& g, int64_t slots) {
   int64_t cost = -1;
   for (int len = 1; len <= 16 && len <= tpz; ++len) {
     const int64_t units = cols * ((tpz + len - 1) / len);
-    const int64_t c = (units + slots - 1) / slots * (2 * len + 1);
+    const int64_t rounds = (units + slots - 1) / slots;
+    const int64_t c = rounds * (4 * len + 2) + (rounds > 1 ? 3 * len : 0);
     if (cost < 0 || c <= cost) {
       cost = c;
       best = len;

@@ -25,6 +25,9 @@ __host__ __device__ inline int weight_slices(int batch) {
   return s < 16 ? 16 : (s > kWSlicesMax ? kWSlicesMax : s);
 }
 
+// doubles per slice of the mass-sum pass: sum w, sum w^2, (largest mass, flag)
+constexpr int kWPartDoubles = 3;
+
 // Geometry and per-call constants that device code needs.
 struct Geom {
   int n;          // N
@@ -76,12 +79,11 @@ struct Buffers {
   uint32_t* bcnt;          // batch * nb^3 bucket counts
   uint4* trecs;            // max_particles records in super-bucket order (two-level sort)
   uint32_t* hsup;          // kMaxSortBlocks x nsup block-major histograms / offsets,
-                           // then the nsup + 1 super-bucket starts
+                           // then the nsup + 1 super-bucket starts and the nsup totals
   uint32_t* scan_tmp;      // scan block sums
   uint32_t* stats;         // [0] largest bucket count of the last sort, [1] tile counter,
                            // [4] largest mass (float bits), [5] nonzero if a mass is
-                           // negative or not finite, [6] fraction bits of the
-                           // deposit's 32-bit fixed point
+                           // negative or not finite
   float2* tw_n;            // exp(-2 pi i n / N)
   float2* tw_nz;           // exp(-2 pi i n / nz)
   float* inv_w2;           // 1 / W_1D(m(i))^2 for FFT index i (N entries)
@@ -95,7 +97,7 @@ struct Buffers {
                            // (N_P, N_P for equal masses)
   float* sw;               // max_particles masses / largest mass, bucket order (weighted handles)
   float* tw;               // max_particles masses in super-bucket order (weighted, two-level)
-  double* wpart;           // batch x weight_slices(batch) x 2 partial mass sums (weighted)
+  double* wpart;           // batch x weight_slices(batch) x kWPartDoubles partial mass sums (weighted)
   float2* cbuf;            // batch x N x N x (N/2+1) combined C(m) (interlace codes 2, 3)
   double* coef;            // batch * kMaxBins adjoint coefficients
   uint64_t* mode_partials_n;  // kMaxBinBlocks * kMaxBins
@@ -133,15 +135,13 @@ __device__ __forceinline__ double grid_coord(double x, double box, double inv) {
 
 // ---- launchers (return hipError_t of the last launch) ----
 hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t s);
-// particle counts per set; norm = (N_P, N_P) per set (equal masses)
-hipError_t launch_set_counts(const int64_t* offsets, int64_t n_total, int batch, int64_t* np,
-                             double* norm, hipStream_t s);
 // masses w (original order): norm = (W, sum w^2) per set in a fixed summation
 // order, stats[4] = largest mass, stats[5] = flag for invalid masses
 hipError_t launch_weight_stats(const float* w, const int64_t* offsets, int64_t n_total, int batch,
                                double* wpart, double* norm, uint32_t* stats, hipStream_t s);
-// w: masses in original order (null: equal masses); their bucket-order
-// copy, divided by the largest mass, goes to b.sw
+// bucket sort, and before it the counts per set (b.np) and norms (b.norm).
+// w: masses in original order (null: equal masses); their sums go to b.norm and
+// their bucket-order copy, divided by the largest mass, to b.sw
 hipError_t launch_sort(const Geom& g, const void* pos, est_dtype dt, const int64_t* offsets,
                        int64_t n_total, const float* w, const Buffers& b, hipStream_t s);
 // from the sort's records (any position type); weighted: read b.sw and

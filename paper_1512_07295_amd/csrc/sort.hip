@@ -27,30 +27,35 @@ hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t s) {
   return hipGetLastError();
 }
 
-__global__ void k_set_counts(const int64_t* offsets, int64_t n_total, int batch, int64_t* np,
-                             double* norm) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= batch) return;
-  const int64_t c = offsets ? (offsets[i + 1] - offsets[i]) : n_total;
-  np[i] = c;
-  norm[2 * i] = (double)c;
-  norm[2 * i + 1] = (double)c;
+// particle counts per set and norm = (N_P, N_P) (equal masses), and the sort's
+// statistics cleared (stats[0..3]); by one workgroup
+__device__ __forceinline__ void set_counts(const int64_t* __restrict__ offsets, int64_t n_total,
+                                           int batch, int64_t* __restrict__ np,
+                                           double* __restrict__ norm, uint32_t* __restrict__ stats) {
+  if (threadIdx.x < 4) stats[threadIdx.x] = 0u;
+  for (int i = threadIdx.x; i < batch; i += blockDim.x) {
+    const int64_t c = offsets ? (offsets[i + 1] - offsets[i]) : n_total;
+    np[i] = c;
+    norm[2 * i] = (double)c;
+    norm[2 * i + 1] = (double)c;
+  }
 }
 
-hipError_t launch_set_counts(const int64_t* offsets, int64_t n_total, int batch, int64_t* np,
-                             double* norm, hipStream_t s) {
-  hipLaunchKernelGGL(k_set_counts, dim3((batch + 63) / 64), dim3(64), 0, s, offsets, n_total,
-                     batch, np, norm);
-  return hipGetLastError();
+__global__ __launch_bounds__(256) void k_set_counts(const int64_t* offsets, int64_t n_total,
+                                                    int batch, int64_t* np, double* norm,
+                                                    uint32_t* stats) {
+  set_counts(offsets, n_total, batch, np, norm, stats);
 }
 
 // ------------------------------------------------------------------ masses
 // Per set, weight_slices(batch) workgroups each sum w and w^2 over a fixed
 // slice of the set's particles (strided per thread, then a fixed tree over
-// the workgroup), and a second pass adds the slices in order: the totals
-// depend on the batch size only, not on scheduling.  The largest mass goes to stats[4] (non-negative
-// floats order like their bit patterns) and any negative, NaN or infinite
-// mass sets stats[5].
+// the workgroup), and a second pass adds the slices in a fixed order: the totals
+// depend on the batch size only, not on scheduling.  Each slice also keeps its
+// largest mass and whether a mass is negative, NaN or infinite; the second
+// pass takes them to stats[4] (non-negative floats order like their bit
+// patterns) and stats[5].  One device-scope atomic per set: one per wave of
+// every slice, all on one address, took 40 of the 52 us for 2M masses.
 constexpr int kWThreads = 256;
 
 __global__ __launch_bounds__(kWThreads) void k_weight_stats(const float* __restrict__ w,
@@ -59,7 +64,9 @@ __global__ __launch_bounds__(kWThreads) void k_weight_stats(const float* __restr
                                                             double* __restrict__ wpart,
                                                             uint32_t* __restrict__ stats) {
   __shared__ double sa[kWThreads / 64], sb[kWThreads / 64];
+  __shared__ uint32_t sm[kWThreads / 64], sbad[kWThreads / 64];
   const int m = blockIdx.y, slice = blockIdx.x, ns = gridDim.x;
+  if (m == 0 && slice == 0 && threadIdx.x < 2) stats[4 + threadIdx.x] = 0u;
   const int64_t j0 = offsets ? offsets[m] : 0, j1 = offsets ? offsets[m + 1] : n_total;
   const int64_t len = j1 - j0;
   const int64_t s0 = j0 + len * slice / ns, s1 = j0 + len * (slice + 1) / ns;
@@ -87,44 +94,61 @@ __global__ __launch_bounds__(kWThreads) void k_weight_stats(const float* __restr
   if (lane == 0) {
     sa[wave] = a;
     sb[wave] = b;
-    if (mx > 0.0f) atomicMax(&stats[4], __float_as_uint(mx));
-    if (anybad) atomicOr(&stats[5], 1u);
+    sm[wave] = __float_as_uint(mx);
+    sbad[wave] = anybad ? 1u : 0u;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     double ta = 0.0, tb = 0.0;
+    uint32_t tm = 0u, tbad = 0u;
     for (int i = 0; i < kWThreads / 64; ++i) {
       ta += sa[i];
       tb += sb[i];
+      tm = max(tm, sm[i]);
+      tbad |= sbad[i];
     }
-    double* dst = wpart + 2 * ((int64_t)m * ns + slice);
+    double* dst = wpart + kWPartDoubles * ((int64_t)m * ns + slice);
     dst[0] = ta;
     dst[1] = tb;
+    reinterpret_cast<uint2*>(dst)[2] = make_uint2(tm, tbad);
   }
 }
 
-__global__ void k_weight_final(const double* __restrict__ wpart, int batch, int ns,
-                               double* __restrict__ norm) {
-  const int m = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= batch) return;
+// one wave per set
+__global__ __launch_bounds__(64) void k_weight_final(const double* __restrict__ wpart, int ns,
+                                                     double* __restrict__ norm,
+                                                     uint32_t* __restrict__ stats) {
+  const int m = blockIdx.x, lane = threadIdx.x;
   double ta = 0.0, tb = 0.0;
-  for (int i = 0; i < ns; ++i) {
-    ta += wpart[2 * ((int64_t)m * ns + i)];
-    tb += wpart[2 * ((int64_t)m * ns + i) + 1];
+  uint32_t tm = 0u, bad = 0u;
+  for (int i = lane; i < ns; i += 64) {
+    const double* src = wpart + kWPartDoubles * ((int64_t)m * ns + i);
+    ta += src[0];
+    tb += src[1];
+    const uint2 f = reinterpret_cast<const uint2*>(src)[2];
+    tm = max(tm, f.x);
+    bad |= f.y;
   }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    ta += __shfl_down(ta, off, 64);
+    tb += __shfl_down(tb, off, 64);
+    tm = max(tm, (uint32_t)__shfl_down((int)tm, off, 64));
+    bad |= (uint32_t)__shfl_down((int)bad, off, 64);
+  }
+  if (lane != 0) return;
   norm[2 * m] = ta;
   norm[2 * m + 1] = tb;
+  if (tm) atomicMax(&stats[4], tm);
+  if (bad) atomicOr(&stats[5], 1u);
 }
 
 hipError_t launch_weight_stats(const float* w, const int64_t* offsets, int64_t n_total, int batch,
                                double* wpart, double* norm, uint32_t* stats, hipStream_t s) {
-  hipError_t e = launch_fill_u32(stats + 4, 2, 0u, s);
-  if (e != hipSuccess) return e;
   const int ns = weight_slices(batch);
   hipLaunchKernelGGL(k_weight_stats, dim3(ns, batch), dim3(kWThreads), 0, s, w, offsets,
                      n_total, wpart, stats);
-  hipLaunchKernelGGL(k_weight_final, dim3((batch + 63) / 64), dim3(64), 0, s, wpart, batch, ns,
-                     norm);
+  hipLaunchKernelGGL(k_weight_final, dim3(batch), dim3(64), 0, s, wpart, ns, norm, stats);
   return hipGetLastError();
 }
 
@@ -309,8 +333,13 @@ static hipError_t sort_atomic(const Geom& g, const void* pos, est_dtype dt,
                               const int64_t* offsets, int64_t n_total, const float* w,
                               const Buffers& b, hipStream_t s) {
   const size_t nkeys = (size_t)g.batch * g.nb * g.nb * g.nb;
-  hipError_t e = launch_fill_u32(b.boff, nkeys + 1, 0u, s);
+  hipLaunchKernelGGL(k_set_counts, dim3(1), dim3(256), 0, s, offsets, n_total, g.batch, b.np, b.norm,
+                     b.stats);
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  if (w && (e = launch_weight_stats(w, offsets, n_total, g.batch, b.wpart, b.norm, b.stats, s)) != hipSuccess)
+    return e;
+  if ((e = launch_fill_u32(b.boff, nkeys + 1, 0u, s)) != hipSuccess) return e;
   const unsigned pblocks = (unsigned)((n_total + 255) / 256);
   const unsigned cblocks = (unsigned)((n_total + kCountThreads - 1) / kCountThreads);
   if (dt == EST_F32)
@@ -335,17 +364,22 @@ static hipError_t sort_atomic(const Geom& g, const void* pos, est_dtype dt,
 // ---- two-level sort without device-scope atomics
 // Super-buckets are cubes of g.fb^3 buckets (g.nsup of them).  (A) each of
 // nblk workgroups histograms a contiguous chunk of particles over the
-// super-buckets in LDS; (B) the histograms, laid out super-major, are
-// scanned, giving every (super-bucket, workgroup) pair its output offset;
-// (C) each workgroup re-reads its chunk and moves every particle's record
-// into its super-bucket segment, ranking with LDS counters, and writes the
+// super-buckets in LDS (the first one also writes the set counts); (B) the
+// histogram rows become per-workgroup offsets and column totals, by a column
+// scan or, with few workgroups, in (C); (C) each workgroup scans the totals,
+// re-reads its chunk and moves every particle's record into its super-bucket
+// segment, ranking with LDS counters, and writes the
 // particle's bucket inside the super-bucket beside it (2 bytes); (D) one
 // workgroup per super-bucket counts its particles per bucket from those
 // 2-byte indices, writes the bucket offsets and counts, and moves the
 // records into bucket order.  Buckets are therefore contiguous in z inside a super-bucket;
 // the deposit splits its bucket runs at super-bucket boundaries.
+// Four launches (three with few workgroups): a scan of the totals in three
+// more, and one each for clearing, counts and the deposit's format, cost
+// small sorts 25-35 us (128^3 particles on 256^3: 105 -> 60 us).
 constexpr int kSortThreads = 1024;
 constexpr int kSortBatch = 4;  // particles per thread whose loads are in flight together
+constexpr int kFewSortBlocks = 16;  // super passes that sum the histogram rows themselves
 constexpr int kFineBlocks = 512;  // workgroups of the bucket pass (two per CU of an MI355X)
 
 __device__ __forceinline__ void particle_buckets(double ux, double uy, double uz, const Geom& g,
@@ -369,9 +403,13 @@ template <typename TP>
 __global__ __launch_bounds__(kSortThreads) void k_sort_hist(const TP* __restrict__ pos,
                                                             int64_t n_total,
                                                             const int64_t* __restrict__ offsets,
-                                                            Geom g, int64_t chunk, int nblk,
-                                                            uint32_t* __restrict__ hsup) {
+                                                            Geom g, int64_t chunk,
+                                                            uint32_t* __restrict__ hsup,
+                                                            int64_t* __restrict__ np,
+                                                            double* __restrict__ norm,
+                                                            uint32_t* __restrict__ stats) {
   __shared__ uint32_t hist[kMaxSuper];
+  if (blockIdx.x == 0) set_counts(offsets, n_total, g.batch, np, norm, stats);
   for (int i = threadIdx.x; i < g.nsup; i += kSortThreads) hist[i] = 0u;
   __syncthreads();
   const int64_t j0 = (int64_t)blockIdx.x * chunk;
@@ -406,12 +444,58 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_hist(const TP* __restrict
 template <typename TP>
 __global__ __launch_bounds__(kSortThreads) void k_sort_super(
     const TP* __restrict__ pos, int64_t n_total, const int64_t* __restrict__ offsets, Geom g,
-    int64_t chunk, const uint32_t* __restrict__ hoff, const uint32_t* __restrict__ base,
-    uint4* __restrict__ trec,
-    uint16_t* __restrict__ tfine, const float* __restrict__ w, float* __restrict__ tw) {
+    int64_t chunk, const uint32_t* __restrict__ hoff, const uint32_t* __restrict__ tot,
+    uint32_t* __restrict__ base, uint4* __restrict__ trec, uint16_t* __restrict__ tfine,
+    const float* __restrict__ w, float* __restrict__ tw) {
   __shared__ uint32_t cur[kMaxSuper];
-  for (int i = threadIdx.x; i < g.nsup; i += kSortThreads)
-    cur[i] = base[i] + hoff[(int64_t)blockIdx.x * g.nsup + i];
+  __shared__ uint32_t wtot[kSortThreads / 64];
+  {
+    // every workgroup scans the super-bucket totals for itself (at most 8 per
+    // thread); workgroup 0 keeps the starts for the bucket pass.  Without a
+    // column scan (tot null: few workgroups) the histogram rows are summed here.
+    constexpr int kPer = kMaxSuper / kSortThreads;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int per = (g.nsup + kSortThreads - 1) / kSortThreads;
+    uint32_t c[kPer], pre[kPer], run = 0;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int i = threadIdx.x * per + q;
+      c[q] = pre[q] = 0u;
+      if (q < per && i < g.nsup) {
+        if (tot) {
+          c[q] = tot[i];
+          pre[q] = hoff[(int64_t)blockIdx.x * g.nsup + i];
+        } else {
+          for (unsigned b = 0; b < gridDim.x; ++b) {
+            const uint32_t v = hoff[(int64_t)b * g.nsup + i];
+            c[q] += v;
+            pre[q] += b < blockIdx.x ? v : 0u;
+          }
+        }
+      }
+      run += c[q];
+    }
+    uint32_t incl = run;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t v = (uint32_t)__shfl_up((int)incl, o, 64);
+      if (lane >= o) incl += v;
+    }
+    if (lane == 63) wtot[wave] = incl;
+    __syncthreads();
+    uint32_t start = incl - run;
+    for (int i = 0; i < wave; ++i) start += wtot[i];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int i = threadIdx.x * per + q;
+      if (q < per && i < g.nsup) {
+        cur[i] = start + pre[q];
+        if (blockIdx.x == 0) base[i] = start;
+      }
+      start += c[q];
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) base[g.nsup] = (uint32_t)n_total;
+  }
   __syncthreads();
   const int64_t j0 = (int64_t)blockIdx.x * chunk;
   const int64_t j1 = (j0 + chunk < n_total) ? j0 + chunk : n_total;
@@ -461,9 +545,12 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_fine(
   __shared__ int next_sup;
   // a fixed grid takes the super-buckets in order from a counter (stats[3],
   // zeroed with the sort's statistics), so that the ones in flight are
-  // neighbours and uneven ones balance
-  for (;;) {
-  if (threadIdx.x == 0) next_sup = (int)atomicAdd(&stats[3], 1u);
+  // neighbours and uneven ones balance; with a workgroup for each there is
+  // nothing to take
+  const bool one_each = gridDim.x >= (unsigned)g.nsup;
+  uint32_t mx = 0;  // largest bucket count this thread has seen
+  for (bool done = false; !done; done = one_each) {
+  if (threadIdx.x == 0) next_sup = one_each ? (int)blockIdx.x : (int)atomicAdd(&stats[3], 1u);
   __syncthreads();  // also: the previous super-bucket's scatter is done
   const int sup = next_sup;
   if (sup >= g.nsup) break;
@@ -486,7 +573,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_fine(
   __syncthreads();
   // exclusive scan of hist[0, nf): kPer consecutive buckets per thread
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  uint32_t c[kPer], run = 0, mx = 0;
+  uint32_t c[kPer], run = 0;
 #pragma unroll
   for (int q = 0; q < kPer; ++q) {
     const int f = t * kPer + q;
@@ -501,9 +588,6 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_fine(
     if (lane >= o) incl += v;
   }
   if (lane == 63) wtot[wave] = incl;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) mx = max(mx, (uint32_t)__shfl_down((int)mx, o, 64));
-  if (lane == 0) atomicMax(&stats[0], mx);
   __syncthreads();
   uint32_t before = 0;
   for (int w = 0; w < wave; ++w) before += wtot[w];
@@ -542,6 +626,18 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_fine(
     }
   }
   }
+  // the largest bucket count: one device-scope atomic per workgroup (one per
+  // wave and super-bucket, all on one address, cost small sorts 10-20 us)
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) mx = max(mx, (uint32_t)__shfl_down((int)mx, o, 64));
+  __syncthreads();
+  if (lane == 0) wtot[wave] = mx;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int i = 1; i < kSortThreads / 64; ++i) mx = max(mx, wtot[i]);
+    if (mx) atomicMax(&stats[0], mx);
+  }
 }
 
 // The histograms are stored block-major (h[b][s], b < nblk, s < nsup, so
@@ -560,6 +656,7 @@ __global__ __launch_bounds__(kColThreads) void k_sup_colscan(uint32_t* __restric
   const int b0 = nblk * wave / kColWaves, b1 = nblk * (wave + 1) / kColWaves;
   uint32_t sum = 0;
   if (sup < nsup)
+#pragma unroll 8
     for (int b = b0; b < b1; ++b) sum += h[(int64_t)b * nsup + sup];
   part[wave][lane] = sum;
   __syncthreads();
@@ -570,10 +667,16 @@ __global__ __launch_bounds__(kColThreads) void k_sup_colscan(uint32_t* __restric
     all += v;
   }
   if (sup < nsup) {
-    for (int b = b0; b < b1; ++b) {
-      const uint32_t v = h[(int64_t)b * nsup + sup];
-      h[(int64_t)b * nsup + sup] = run;
-      run += v;
+    // eight rows at a time, their loads issued together
+    for (int b = b0; b < b1; b += 8) {
+      uint32_t v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = b + q < b1 ? h[(int64_t)(b + q) * nsup + sup] : 0u;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        if (b + q < b1) h[(int64_t)(b + q) * nsup + sup] = run;
+        run += v[q];
+      }
     }
     if (wave == 0) tot[sup] = all;
   }
@@ -586,22 +689,26 @@ static hipError_t sort_two_level(const Geom& g, const TP* pos, const int64_t* of
   if (nblk > kMaxSortBlocks) nblk = kMaxSortBlocks;
   const int64_t chunk = (n_total + nblk - 1) / nblk;
   hipLaunchKernelGGL(k_sort_hist<TP>, dim3(nblk), dim3(kSortThreads), 0, s, pos, n_total,
-                     offsets, g, chunk, nblk, b.hsup);
-  // per-block offsets inside each super-bucket, then the super-bucket starts
-  // (base[nsup] = n_total) after the kMaxSortBlocks rows of histograms
-  uint32_t* base = b.hsup + (size_t)g.nsup * kMaxSortBlocks;
-  hipLaunchKernelGGL(k_sup_colscan, dim3((g.nsup + 63) / 64), dim3(kColThreads), 0, s, b.hsup,
-                     g.nsup, nblk, base);
+                     offsets, g, chunk, b.hsup, b.np, b.norm, b.stats);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // the scan's largest-entry output is not a bucket count here
-  if ((e = scan_in_place(base, (size_t)g.nsup + 1, b.scan_tmp, b.stats + 2, s)) != hipSuccess)
+  if (w && (e = launch_weight_stats(w, offsets, n_total, g.batch, b.wpart, b.norm, b.stats, s)) != hipSuccess)
     return e;
+  // after the kMaxSortBlocks rows of histograms: the super-bucket starts
+  // (base[nsup] = n_total) and totals.  Many workgroups: a column scan turns
+  // the rows into per-block offsets and totals; few: the super pass does it.
+  uint32_t* base = b.hsup + (size_t)g.nsup * kMaxSortBlocks;
+  uint32_t* tot = base + g.nsup + 1;
+  const bool few = nblk <= kFewSortBlocks;
+  if (!few)
+    hipLaunchKernelGGL(k_sup_colscan, dim3((g.nsup + 63) / 64), dim3(kColThreads), 0, s, b.hsup,
+                       g.nsup, nblk, tot);
   // the per-particle ranks of the atomic sort are not used here: their
   // buffer holds each particle's bucket inside its super-bucket (2 bytes)
   uint16_t* tfine = reinterpret_cast<uint16_t*>(b.rank);
   hipLaunchKernelGGL(k_sort_super<TP>, dim3(nblk), dim3(kSortThreads), 0, s, pos, n_total,
-                     offsets, g, chunk, b.hsup, (const uint32_t*)base, b.trecs, tfine, w, b.tw);
+                     offsets, g, chunk, b.hsup, few ? nullptr : (const uint32_t*)tot, base, b.trecs, tfine, w,
+                     b.tw);
   hipLaunchKernelGGL(k_sort_fine, dim3(g.nsup < kFineBlocks ? g.nsup : kFineBlocks), dim3(kSortThreads), 0, s, (const uint4*)b.trecs,
                      (const uint16_t*)tfine, g, (const uint32_t*)base, b.recs,
                      b.boff, b.bcnt, b.stats, w ? b.tw : nullptr, b.sw);
@@ -610,8 +717,6 @@ static hipError_t sort_two_level(const Geom& g, const TP* pos, const int64_t* of
 
 hipError_t launch_sort(const Geom& g, const void* pos, est_dtype dt, const int64_t* offsets,
                        int64_t n_total, const float* w, const Buffers& b, hipStream_t s) {
-  hipError_t e = launch_fill_u32(b.stats, 4, 0u, s);
-  if (e != hipSuccess) return e;
   if (g.nsup > kMaxSuper) return sort_atomic(g, pos, dt, offsets, n_total, w, b, s);
   if (dt == EST_F32) return sort_two_level(g, (const float*)pos, offsets, n_total, w, b, s);
   return sort_two_level(g, (const double*)pos, offsets, n_total, w, b, s);
