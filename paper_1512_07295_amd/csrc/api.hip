@@ -683,7 +683,7 @@ est_status estimator_graph_launch(est_handle h) {
 
 static Tune tune_from_index(const int* id, int cus) {
   static const int vals_cols[2] = {8, 16};
-  static const int vals_bins[3] = {256, 1024, 2048};
+  static const int vals_bins[3] = {256, 0, 2048};  // 0: by occupancy
   static const int vals_dep[2] = {512, 1024};
   Tune t;
   t.cus = cus;

@@ -107,7 +107,7 @@ struct Buffers {
 // Launch shapes chosen per handle (the autotuner changes them).
 struct Tune {
   int cols_c = 16;        // lines per workgroup of the strided FFT passes
-  int bin_blocks = 1024;  // reduction workgroups per set in the fused P(k) pass
+  int bin_blocks = 0;     // reduction workgroups per set in the fused P(k) pass (0: by occupancy)
   int dep_threads = 0;    // threads per deposit workgroup (0: chosen per kernel)
   int dep_narrow = 1;     // 32-bit fixed point when provably safe (else 64-bit)
   int dep_xcd = 1;        // consecutive deposit tiles on one XCD (shared L2)

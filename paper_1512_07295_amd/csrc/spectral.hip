@@ -438,30 +438,59 @@ __global__ void k_adjoint_coef(const double* __restrict__ dldp, int n_bins, cons
   coef[o] = (npart > 0.0) ? 2.0 * dldp[o] * vol / ((double)mode_n[b] * npart * npart) : 0.0;
 }
 
+// Workgroups per set of the pair pass.  Each pays a set-up (tables, the
+// column scan) and leaves a row of partial sums, so by default there are as
+// many as the device holds at once, shared by the sets.  With 1024 per set (a
+// round and a third at 1024^3, one row group per workgroup for a batch):
+// 1024^3 2.45 -> 2.06 ms, 480^3 0.60 -> 0.49, 64 sets of 128^3 0.38 -> 0.28.
+// tu.bin_blocks > 0: that many (the autotuner's choice).
+static int resident_blocks(const void* kernel, const Geom& g, const Tune& tu, int threads, size_t lds) {
+  int per_cu = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds) != hipSuccess || per_cu < 1)
+    per_cu = 1;
+  return (tu.cus * per_cu + g.batch - 1) / g.batch;
+}
+
 template <int L, bool IL, int MODE>
-static hipError_t pairs_t(const Geom& g, const Buffers& b, int nblk, int n_dk, int n_bins,
-                          const float2* tw, hipStream_t s) {
+static int pair_blocks(const Geom& g, const Tune& tu, int threads, int ppb) {
+  // interlaced rows hold N complex values, packed rows N/2
+  const int64_t npairs = (int64_t)g.n * g.n / 2 + 2;
+  const int64_t groups = (npairs + ppb - 1) / ppb;
+  int64_t nblk = tu.bin_blocks;
+  if (nblk <= 0) nblk = resident_blocks((const void*)k_pairs<L, IL, MODE>, g, tu, threads, 0);
+  if (nblk > groups) nblk = groups;
+  if (nblk > kMaxBinBlocks) nblk = kMaxBinBlocks;
+  return (int)nblk;
+}
+
+// launches the pair pass; *nblk receives its workgroups per set (rows of partial sums)
+template <int L, bool IL, int MODE>
+static hipError_t pairs_t(const Geom& g, const Buffers& b, const Tune& tu, int n_dk, int n_bins,
+                          const float2* tw, int* nblk, hipStream_t s) {
   RtLine rt{};
-  int threads = 0;
+  int threads = 0, ppb = 0;
   if constexpr (L == 0) {
     if (!make_rt_line(g.nz, &rt)) return hipErrorInvalidValue;
-    threads = 2 * rt_pairs_per_block(rt.tpl) * rt.tpl;
+    ppb = rt_pairs_per_block(rt.tpl);
+    threads = 2 * ppb * rt.tpl;
   } else {
+    ppb = PairShape<L>::PPB;
     threads = PairShape<L>::THREADS;
   }
-  hipLaunchKernelGGL((k_pairs<L, IL, MODE>), dim3(nblk, g.batch), dim3(threads), 0, s,
+  *nblk = pair_blocks<L, IL, MODE>(g, tu, threads, ppb);
+  hipLaunchKernelGGL((k_pairs<L, IL, MODE>), dim3(*nblk, g.batch), dim3(threads), 0, s,
                      b.grid, g, tw, b.phase, b.inv_w2, n_dk, n_bins, b.partials, b.coef, rt);
   return hipGetLastError();
 }
 
 template <int MODE>
-static hipError_t pairs_dispatch(const Geom& g, const Buffers& b, int nblk, int n_dk, int n_bins,
-                                 hipStream_t s) {
+static hipError_t pairs_dispatch(const Geom& g, const Buffers& b, const Tune& tu, int n_dk, int n_bins,
+                                 int* nblk, hipStream_t s) {
   const float2* tw = b.tw_nz;
 #define FSEST_PAIRS_CASE(LL)                                                     \
   case LL:                                                                       \
-    return g.il ? pairs_t<LL, true, MODE>(g, b, nblk, n_dk, n_bins, tw, s)       \
-                : pairs_t<LL, false, MODE>(g, b, nblk, n_dk, n_bins, tw, s);
+    return g.il ? pairs_t<LL, true, MODE>(g, b, tu, n_dk, n_bins, tw, nblk, s)   \
+                : pairs_t<LL, false, MODE>(g, b, tu, n_dk, n_bins, tw, nblk, s);
   switch ((g.nz & (g.nz - 1)) == 0 ? g.nz : 0) {
     FSEST_PAIRS_CASE(4)
     FSEST_PAIRS_CASE(8)
@@ -478,30 +507,6 @@ static hipError_t pairs_dispatch(const Geom& g, const Buffers& b, int nblk, int 
   return hipErrorInvalidValue;
 }
 
-static int pair_blocks(const Geom& g, const Tune& tu) {
-  // interlaced rows hold N complex values, packed rows N/2
-  int64_t npairs = (int64_t)g.n * g.n / 2 + 2;
-  int ppb;
-  switch (g.nz) {
-    case 4: ppb = PairShape<4>::PPB; break;
-    case 8: ppb = PairShape<8>::PPB; break;
-    case 16: ppb = PairShape<16>::PPB; break;
-    case 32: ppb = PairShape<32>::PPB; break;
-    case 64: ppb = PairShape<64>::PPB; break;
-    case 128: ppb = PairShape<128>::PPB; break;
-    case 256: ppb = PairShape<256>::PPB; break;
-    case 512: ppb = PairShape<512>::PPB; break;
-    case 1024: ppb = PairShape<1024>::PPB; break;
-    default: ppb = rt_pairs_per_block((g.nz + 15) / 16); break;
-  }
-  int64_t groups = (npairs + ppb - 1) / ppb;
-  int64_t nblk = tu.bin_blocks;
-  if (nblk > groups) nblk = groups;
-  if (nblk > kMaxBinBlocks) nblk = kMaxBinBlocks;
-  if (nblk < 1) nblk = 1;
-  return (int)nblk;
-}
-
 // Shell sums of w |C(m)|^2 / W(m)^2 over the half space for more than two
 // grids.  A workgroup takes row pairs (x, y), (-x, -y) as the fused pair
 // kernel does and stages both rows of every slab in LDS: with FFT, TPL
@@ -510,7 +515,6 @@ static int pair_blocks(const Geom& g, const Tune& tu) {
 // spectra are loaded cooperatively.  Then half the threads finish the
 // half-space modes of each row (runs of m_z per thread, shells advancing
 // along the run).
-constexpr int kMultiBlocks = 1024;
 constexpr int kMultiThreads = 256;
 
 template <int L, bool FFT>
@@ -628,8 +632,8 @@ __global__ __launch_bounds__(1024) void k_multi_pairs(
 }
 
 template <int L, bool FFT>
-static hipError_t multi_pairs_t(const Geom& g, const Buffers& b, int n_dk, int n_bins,
-                                hipStream_t s) {
+static hipError_t multi_pairs_t(const Geom& g, const Buffers& b, const Tune& tu, int n_dk, int n_bins,
+                                int* nblk, hipStream_t s) {
   RtLine rt{};
   int threads = kMultiThreads;
   if constexpr (FFT) {
@@ -650,24 +654,29 @@ static hipError_t multi_pairs_t(const Geom& g, const Buffers& b, int n_dk, int n
                         (int)(sizeof(float2) * 2 * 4 * (1024 + 64 + 1)));
     attr_set = true;
   }
-  hipLaunchKernelGGL((k_multi_pairs<L, FFT>), dim3(kMultiBlocks, g.batch), dim3(threads), lds, s,
+  const int64_t npairs = (int64_t)g.n * g.n / 2 + 2;
+  int64_t blocks = resident_blocks((const void*)k_multi_pairs<L, FFT>, g, tu, threads, lds);
+  if (blocks > npairs) blocks = npairs;
+  if (blocks > kMaxBinBlocks) blocks = kMaxBinBlocks;
+  *nblk = (int)blocks;
+  hipLaunchKernelGGL((k_multi_pairs<L, FFT>), dim3(*nblk, g.batch), dim3(threads), lds, s,
                      b.grid, g, b.tw_nz, b.phase, b.inv_w2, n_dk, n_bins, b.partials, rt);
   return hipGetLastError();
 }
 
-static hipError_t multi_pairs_dispatch(const Geom& g, const Buffers& b, bool do_fft, int n_dk,
-                                       int n_bins, hipStream_t s) {
-  if (!do_fft) return multi_pairs_t<0, false>(g, b, n_dk, n_bins, s);
+static hipError_t multi_pairs_dispatch(const Geom& g, const Buffers& b, const Tune& tu, bool do_fft, int n_dk,
+                                       int n_bins, int* nblk, hipStream_t s) {
+  if (!do_fft) return multi_pairs_t<0, false>(g, b, tu, n_dk, n_bins, nblk, s);
   switch ((g.nz & (g.nz - 1)) == 0 ? g.nz : 0) {
-    case 8: return multi_pairs_t<8, true>(g, b, n_dk, n_bins, s);
-    case 16: return multi_pairs_t<16, true>(g, b, n_dk, n_bins, s);
-    case 32: return multi_pairs_t<32, true>(g, b, n_dk, n_bins, s);
-    case 64: return multi_pairs_t<64, true>(g, b, n_dk, n_bins, s);
-    case 128: return multi_pairs_t<128, true>(g, b, n_dk, n_bins, s);
-    case 256: return multi_pairs_t<256, true>(g, b, n_dk, n_bins, s);
-    case 512: return multi_pairs_t<512, true>(g, b, n_dk, n_bins, s);
-    case 1024: return multi_pairs_t<1024, true>(g, b, n_dk, n_bins, s);
-    default: return multi_pairs_t<0, true>(g, b, n_dk, n_bins, s);
+    case 8: return multi_pairs_t<8, true>(g, b, tu, n_dk, n_bins, nblk, s);
+    case 16: return multi_pairs_t<16, true>(g, b, tu, n_dk, n_bins, nblk, s);
+    case 32: return multi_pairs_t<32, true>(g, b, tu, n_dk, n_bins, nblk, s);
+    case 64: return multi_pairs_t<64, true>(g, b, tu, n_dk, n_bins, nblk, s);
+    case 128: return multi_pairs_t<128, true>(g, b, tu, n_dk, n_bins, nblk, s);
+    case 256: return multi_pairs_t<256, true>(g, b, tu, n_dk, n_bins, nblk, s);
+    case 512: return multi_pairs_t<512, true>(g, b, tu, n_dk, n_bins, nblk, s);
+    case 1024: return multi_pairs_t<1024, true>(g, b, tu, n_dk, n_bins, nblk, s);
+    default: return multi_pairs_t<0, true>(g, b, tu, n_dk, n_bins, nblk, s);
   }
 }
 
@@ -675,16 +684,17 @@ hipError_t launch_power(const Geom& g, const Buffers& b, const Tune& tu, bool do
                         int n_bins, int subtract_shot, double* k, double* p, int64_t* nmodes,
                         hipStream_t s) {
   if (g.npair > 1) {
-    hipError_t e = multi_pairs_dispatch(g, b, do_fft, n_dk, n_bins, s);
+    int nblk = 0;
+    hipError_t e = multi_pairs_dispatch(g, b, tu, do_fft, n_dk, n_bins, &nblk, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_power_finalize, dim3(n_bins, g.batch), dim3(64), 0, s, b.partials,
-                       kMultiBlocks, n_bins, b.mode_n, b.mode_k, b.norm, g.box, subtract_shot, k, p,
+                       nblk, n_bins, b.mode_n, b.mode_k, b.norm, g.box, subtract_shot, k, p,
                        nmodes);
     return hipGetLastError();
   }
-  const int nblk = pair_blocks(g, tu);
-  hipError_t e = do_fft ? pairs_dispatch<0>(g, b, nblk, n_dk, n_bins, s)
-                        : pairs_dispatch<1>(g, b, nblk, n_dk, n_bins, s);
+  int nblk = 0;
+  hipError_t e = do_fft ? pairs_dispatch<0>(g, b, tu, n_dk, n_bins, &nblk, s)
+                        : pairs_dispatch<1>(g, b, tu, n_dk, n_bins, &nblk, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_power_finalize, dim3(n_bins, g.batch), dim3(64), 0, s,
                      b.partials, nblk, n_bins, b.mode_n, b.mode_k, b.norm, g.box, subtract_shot, k, p,
@@ -792,8 +802,8 @@ hipError_t launch_adjoint_spectrum(const Geom& g, const Buffers& b, const Tune& 
                      n_bins, b.mode_n, b.norm, g.box, b.coef);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int nblk = pair_blocks(g, tu);
-  return pairs_dispatch<2>(g, b, nblk, n_dk, n_bins, s);
+  int nblk = 0;
+  return pairs_dispatch<2>(g, b, tu, n_dk, n_bins, &nblk, s);
 }
 
 // ------------------------------------------------------------------ mode table
