@@ -193,58 +193,45 @@ __global__ __launch_bounds__(256) void k_fft_rows_rt(float2* __restrict__ data, 
   const int line = threadIdx.x / tpl, t = threadIdx.x % tpl;
   const int64_t row = (int64_t)blockIdx.x * lpb + line;
   const bool valid = row < nrows;
-  float2* p = data + (row / rows_per_plane) * plane_stride + (row % rows_per_plane) * L;
-  float2 v[16];
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int j = t + e * tpl;
-    v[e] = (valid && j < L) ? p[j] : make_float2(0.f, 0.f);
-  }
-  line_fft_rt<DIR, 1>(v, t, lds + line * rowp, pl, tw);
-  if (valid) {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int j = t + e * tpl;
-      if (j < L) p[j] = v[e];
-    }
-  }
+  // lines past the last one read it too, and store nothing
+  const int64_t rr = valid ? row : nrows - 1;
+  float2* p = data + (rr / rows_per_plane) * plane_stride + (rr % rows_per_plane) * L + t;
+  line_fft_rt_io<DIR, 1, kRtLoad, true>([&](int u) { return p[u]; },
+                               [&](int u, float2 v) {
+                                 if (valid) p[u] = v;
+                               },
+                               t, lds + line * rowp, pl, tw);
 }
 
-// strided lines: C adjacent lines per workgroup, interleaved in LDS; the
-// last chunk of a row may be partial (lines past `inner` load zeros and are
-// not stored)
+// strided lines: C adjacent lines per workgroup, interleaved in LDS (480^3,
+// 16 x 6 x 5 in three LDS round trips and the x pass spread over y like the
+// compile-time one: x 0.52 -> 0.44 ms, y 0.47 -> 0.39, 3.6 -> 4.1-4.5 TB/s); the
+// last chunk of a row may be partial (lines past `inner` read the last one and
+// are not stored)
 template <int DIR, int C>
 __global__ __launch_bounds__(1024) void k_fft_cols_rt(float2* __restrict__ data, int64_t elem_stride,
                                                       int64_t inner, int64_t chunks_per_outer,
-                                                      int64_t outer_stride,
+                                                      int64_t outer_stride, int64_t spread,
                                                       const float2* __restrict__ tw, RtLine pl) {
   extern __shared__ float2 lds_dyn[];
   const int L = pl.L, tpl = pl.tpl;
   const int c = threadIdx.x % C, t = threadIdx.x / C;
   const int64_t outer = blockIdx.x / chunks_per_outer;
-  const int64_t ic = blockIdx.x % chunks_per_outer;
+  const int64_t ib = blockIdx.x % chunks_per_outer;
+  const int64_t ic = spread ? (ib % spread) * (chunks_per_outer / spread) + ib / spread : ib;
   const bool valid = ic * C + c < inner;
-  const float2* p = data + outer * outer_stride + ic * C + c;
-  float2 v[16];
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int j = t + e * tpl;
-    v[e] = (valid && j < L) ? p[(int64_t)j * elem_stride] : make_float2(0.f, 0.f);
-  }
-  line_fft_rt<DIR, C>(v, t, lds_dyn + c, pl, tw);
-  // the store addresses are formed again from a base the compiler cannot
-  // match with the loads' (an empty asm statement), so that the 16 64-bit
-  // load addresses are not kept live across the transform (they spilled)
-  float2* ds = data;
-  asm volatile("" : "+s"(ds));
-  float2* q = ds + outer * outer_stride + ic * C + c;
-  if (valid) {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int j = t + e * tpl;
-      if (j < L) q[(int64_t)j * elem_stride] = v[e];
-    }
-  }
+  // addresses: a uniform base per element index u plus one 32-bit lane offset
+  // (t < L / 16 elements, under 2^32 bytes for every grid up to 1024^3)
+  char* base = (char*)(data + outer * outer_stride + ic * C);
+  const int cl = valid ? c : (int)(inner - ic * C) - 1;
+  const uint32_t voff = (uint32_t)((cl + (int64_t)t * elem_stride) * (int64_t)sizeof(float2));
+  const int64_t step = elem_stride * (int64_t)sizeof(float2);
+  line_fft_rt_io<DIR, C, kRtLoad, true>(
+      [&](int u) { return *(const float2*)(base + u * step + voff); },
+      [&](int u, float2 v) {
+        if (valid) *(float2*)(base + u * step + voff) = v;
+      },
+      t, lds_dyn + c, pl, tw);
 }
 
 template <int DIR>
@@ -261,11 +248,12 @@ static hipError_t rows_rt(int L, float2* data, int64_t nrows, int rpp, int64_t p
 
 template <int DIR>
 static hipError_t cols_rt(int L, float2* data, int64_t elem_stride, int64_t inner, int64_t outer,
-                          int64_t outer_stride, const float2* tw, hipStream_t s) {
+                          int64_t outer_stride, int64_t spread, const float2* tw, hipStream_t s) {
   constexpr int C = 16;  // 16 * tpl <= 1024 threads and 16 L <= 16384 elements of LDS
   RtLine pl;
   if (!make_rt_line(L, &pl) || C * pl.tpl > 1024) return hipErrorInvalidValue;
   const int64_t chunks = (inner + C - 1) / C;
+  if (spread && inner % (spread * C) != 0) spread = 0;
   const size_t lds = sizeof(float2) * (size_t)L * C;
   static bool attr_set = false;
   if (!attr_set) {
@@ -274,7 +262,7 @@ static hipError_t cols_rt(int L, float2* data, int64_t elem_stride, int64_t inne
     attr_set = true;
   }
   hipLaunchKernelGGL((k_fft_cols_rt<DIR, C>), dim3((unsigned)(chunks * outer)), dim3(C * pl.tpl),
-                     lds, s, data, elem_stride, inner, chunks, outer_stride, tw, pl);
+                     lds, s, data, elem_stride, inner, chunks, outer_stride, spread, tw, pl);
   return hipGetLastError();
 }
 
@@ -311,7 +299,7 @@ static hipError_t cols_dir(int L, float2* data, int64_t elem_stride, int64_t inn
     FSEST_COLS_CASE(256)
     FSEST_COLS_CASE(512)
     FSEST_COLS_CASE(1024)
-    default: return cols_rt<DIR>(L, data, elem_stride, inner, outer, outer_stride, tw, s);
+    default: return cols_rt<DIR>(L, data, elem_stride, inner, outer, outer_stride, spread, tw, s);
   }
 #undef FSEST_COLS_CASE
 }

@@ -235,12 +235,14 @@ __device__ __forceinline__ void line_fft_1024_r32(float2 (&v)[32], int t, float2
 // ---------------------------------------------------------------- mixed radix
 // Lengths L = 2^a 3^b 5^c that are not powers of two use a plan chosen at
 // run time: Stockham stages of radix 16, 8, 4, 2 (the power-of-two part,
-// largest first) then 3 and 5, the line held by tpl = ceil(L / 16) threads.
-// Thread t holds elements t + e * tpl (e < 16, element < L) in registers on
-// entry and exit, as for the power-of-two lines; between stages the line
-// lives in LDS in natural order, each thread reading the inputs of its
-// butterflies (at most ceil(16 / R) of radix R), then, after a barrier,
-// writing their outputs.
+// largest first) then 3 and 5, neighbouring ones whose product is at most 16
+// done together in registers (6 = 2 x 3, 9 = 3 x 3, 10 = 2 x 5, 12 = 4 x 3,
+// 15 = 3 x 5), the line held by tpl = ceil(L / 16) threads, each with at most
+// ceil(16 / R) butterflies of radix R.  A first stage below 16 takes its inputs
+// straight from where the line lies and the last one stores straight to it
+// (or leaves the line in LDS in natural order); between stages the line goes
+// through LDS.  480 = 16 x 6 x 5: three LDS round trips, where stage by stage
+// (16, 2, 3, 5) with the line loaded to and stored from LDS they were five.
 constexpr int kRtMaxStages = 12;
 struct RtLine {
   int L;
@@ -289,92 +291,252 @@ __device__ __forceinline__ void dft_any(float2* a) {
   else Dft<R, DIR>::run(a);
 }
 
-// One Stockham stage of radix R over a line of length L in LDS, after
-// sub-transforms of length ns: butterfly j reads elements j + q L/R, applies
-// the twiddles w^(q k), k = j mod ns, w = exp(DIR 2 pi i / (ns R)), and writes
-// its outputs to (j - k) R + k + q ns.
 // j mod ns as j - floor(j m / 2^32) ns with m = floor((2^32 - 1) / ns) + 1
 // (ns >= 2): exact for j ns < 2^32, far above these lines (j < L <= 1024)
 __device__ __forceinline__ int rt_mod(int j, int ns, uint32_t m) {
   return ns > 1 ? j - (int)__umulhi((uint32_t)j, m) * ns : 0;
 }
 
-template <int R, int DIR, int LS>
-__device__ __forceinline__ void rt_stage(float2* lb, int t, int tpl, int L, int ns, uint32_t nsm,
-                                         const float2* __restrict__ tw) {
+// Keeps the compiler from fusing a twiddle product into the butterfly that
+// follows (an empty asm statement): the rounding of a line's values then does
+// not depend on how its stages are grouped.
+__device__ __forceinline__ void rounded(float2& v) { asm("" : "+v"(v.x), "+v"(v.y)); }
+
+// First factor of a stage's radix: R = R1 R2, R1 done first.
+constexpr int rt_first(int r) { return r == 6 || r == 10 ? 2 : (r == 9 || r == 15 ? 3 : (r == 12 ? 4 : r)); }
+
+// One butterfly of a Stockham stage of radix R = R1 R2 after sub-transforms of
+// length ns: input q of butterfly j is element j + q L/R, k = j mod ns; for a
+// radix-R1 stage followed by a radix-R2 one these are R2 butterflies of the
+// first (m = q mod R2) and then R1 of the second, with k + q1 ns.  The twiddles
+// of a stage are w^(q k), w = exp(DIR 2 pi i / (ns R)).  Afterwards a[i] is
+// the output at (j - k) R + k + rt_out(i) ns.
+template <int R, int DIR, bool FIRST>
+__device__ __forceinline__ void rt_butterfly(float2 (&a)[R], int k, int L, int ns,
+                                             const float2* __restrict__ tw) {
+  constexpr int R1 = rt_first(R), R2 = R / R1;
+  auto twiddle = [&](float2& v, int idx) {
+    float2 w = tw[idx];
+    if constexpr (DIR > 0) w.y = -w.y;
+    v = cmul(v, w);
+    rounded(v);
+  };
+  const int step1 = FIRST ? 0 : L / (ns * R1);
+#pragma unroll
+  for (int m = 0; m < R2; ++m) {
+    float2 b[R1];
+#pragma unroll
+    for (int q = 0; q < R1; ++q) b[q] = a[m + q * R2];
+    if constexpr (!FIRST) {
+#pragma unroll
+      for (int q = 1; q < R1; ++q) twiddle(b[q], q * k * step1);
+    }
+    dft_any<R1, DIR>(b);
+#pragma unroll
+    for (int q = 0; q < R1; ++q) {
+      a[m + q * R2] = b[q];
+      if constexpr (R2 > 1) rounded(a[m + q * R2]);
+    }
+  }
+  if constexpr (R2 > 1) {
+    const int step2 = L / (ns * R);
+#pragma unroll
+    for (int q = 0; q < R1; ++q) {
+      float2 b[R2];
+#pragma unroll
+      for (int m = 0; m < R2; ++m) b[m] = a[m + q * R2];
+#pragma unroll
+      for (int m = 1; m < R2; ++m) twiddle(b[m], m * (k + q * ns) * step2);
+      dft_any<R2, DIR>(b);
+#pragma unroll
+      for (int m = 0; m < R2; ++m) a[m + q * R2] = b[m];
+    }
+  }
+}
+template <int R>
+constexpr int rt_out(int i) {
+  return i / (R / rt_first(R)) + (i % (R / rt_first(R))) * rt_first(R);
+}
+
+// A stage over the line.  SRC: kRtLoad, the first stage (ns = 1), element t + u
+// of the line from load(u) (u the same for every thread); kRtFirst, the first
+// stage from LDS; kRtMid, a later one from LDS.  LAST: element t + u goes to
+// store(u, value) (ns R = L); else to LDS, with barriers so that every thread
+// may read it afterwards.
+constexpr int kRtLoad = 0, kRtFirst = 1, kRtMid = 2;
+
+template <int R, int DIR, int LS, int SRC, bool LAST, typename Load, typename Store>
+__device__ __forceinline__ void rt_stage(Load&& load, Store&& store, float2* lb, int t, int tpl, int L,
+                                         int ns, const float2* __restrict__ tw) {
   constexpr int NB = (16 + R - 1) / R;
+  constexpr bool FIRST = SRC != kRtMid;
   const int nbf = L / R;
-  const int step = L / (ns * R);
+  const uint32_t nsm = !FIRST && ns > 1 ? 0xFFFFFFFFu / (uint32_t)ns + 1u : 0u;
   float2 a[NB][R];
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
     const int j = t + i * tpl;
     if (j < nbf) {
-      const int k = rt_mod(j, ns, nsm);
 #pragma unroll
-      for (int q = 0; q < R; ++q) a[i][q] = lb[lds_index<LS>(j + q * nbf)];
-      if (ns > 1) {
-#pragma unroll
-        for (int q = 1; q < R; ++q) {
-          float2 w = tw[q * k * step];
-          if constexpr (DIR > 0) w.y = -w.y;
-          a[i][q] = cmul(a[i][q], w);
-        }
+      for (int q = 0; q < R; ++q) {
+        if constexpr (SRC == kRtLoad) a[i][q] = load(i * tpl + q * nbf);
+        else a[i][q] = lb[lds_index<LS>(j + q * nbf)];
       }
-      dft_any<R, DIR>(a[i]);
     }
   }
-  __syncthreads();
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
     const int j = t + i * tpl;
-    if (j < nbf) {
-      const int k = rt_mod(j, ns, nsm);
-      const int base = (j - k) * R + k;
+    if (j < nbf) rt_butterfly<R, DIR, FIRST>(a[i], FIRST ? 0 : rt_mod(j, ns, nsm), L, FIRST ? 1 : ns, tw);
+  }
+  if constexpr (LAST) {
 #pragma unroll
-      for (int q = 0; q < R; ++q) lb[lds_index<LS>(base + q * ns)] = a[i][q];
+    for (int i = 0; i < NB; ++i)
+      if (t + i * tpl < nbf) {
+#pragma unroll
+        for (int q = 0; q < R; ++q) store(i * tpl + rt_out<R>(q) * nbf, a[i][q]);
+      }
+  } else {
+    if constexpr (SRC != kRtLoad) __syncthreads();  // every input is read
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int j = t + i * tpl;
+      if (j < nbf) {
+        const int k = FIRST ? 0 : rt_mod(j, ns, nsm);
+        const int base = (j - k) * R + k;
+#pragma unroll
+        for (int q = 0; q < R; ++q) lb[lds_index<LS>(base + rt_out<R>(q) * (FIRST ? 1 : ns))] = a[i][q];
+      }
     }
+    __syncthreads();
+  }
+}
+
+// A radix-16 stage, from LDS to LDS (ns = 1 for the first).  Which product of
+// a constant twiddle the compiler rounds (the other one goes into the fused
+// multiply-add) follows from the code around the butterfly, so it has one form
+// wherever it stands in a plan.
+template <int DIR, int LS>
+__device__ __forceinline__ void rt_stage16(float2* lb, int t, int L, int ns,
+                                           const float2* __restrict__ tw) {
+  const int nbf = L / 16;
+  const uint32_t nsm = ns > 1 ? 0xFFFFFFFFu / (uint32_t)ns + 1u : 0u;
+  const int step = L / (ns * 16);
+  float2 a[16];
+  const int j = t;
+  if (j < nbf) {
+    const int k = rt_mod(j, ns, nsm);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) a[q] = lb[lds_index<LS>(j + q * nbf)];
+    if (ns > 1) {
+#pragma unroll
+      for (int q = 1; q < 16; ++q) {
+        float2 w = tw[q * k * step];
+        if constexpr (DIR > 0) w.y = -w.y;
+        a[q] = cmul(a[q], w);
+      }
+    }
+    Dft<16, DIR>::run(a);
+  }
+  __syncthreads();
+  if (j < nbf) {
+    const int k = rt_mod(j, ns, nsm);
+    const int base = (j - k) * 16 + k;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) lb[lds_index<LS>(base + q * ns)] = a[q];
   }
   __syncthreads();
 }
 
-// Whole-line FFT of a run-time plan; every thread of the workgroup calls it.
-template <int DIR, int LS>
-__device__ __forceinline__ void line_fft_rt(float2 (&v)[16], int t, float2* lb, const RtLine& pl,
-                                            const float2* __restrict__ tw) {
-  const int L = pl.L, tpl = pl.tpl;
+// Whole-line FFT of a run-time plan; every thread of the workgroup calls it,
+// with its LDS free (SRC kRtLoad, load(u): element t + u) or holding the line
+// in natural order (kRtFirst).  store(u, v): element t + u, or (STORE false)
+// the line is left in LDS in natural order for every thread.
+template <int DIR, int LS, int SRC, bool STORE, typename Load, typename Store>
+__device__ __forceinline__ void line_fft_rt_io(Load&& load, Store&& store, int t, float2* lb,
+                                               const RtLine& pl, const float2* __restrict__ tw) {
+  int L = pl.L, tpl = pl.tpl;
+  const int nst = pl.nst;
+  const bool direct = STORE && nst == 1;
+  // the thread index, the length and the threads per line pass through an empty
+  // asm statement in every stage, so that the compiler forms each stage's
+  // offsets in that stage instead of hoisting those of every radix out of the
+  // loops (which spills)
+  int ts = t;
+  asm volatile("" : "+v"(ts), "+s"(L), "+s"(tpl));
+  // a first radix of 16 reads the line from LDS
+  const bool via_lds = pl.radix[0] == 16;
+  if (SRC == kRtLoad && via_lds) {
+    float2 v[16];  // all loads in flight together
 #pragma unroll
-  for (int e = 0; e < 16; ++e)
-    if (t + e * tpl < L) lb[lds_index<LS>(t + e * tpl)] = v[e];
-  __syncthreads();
-  int ns = 1;
-  for (int s = 0; s < pl.nst; ++s) {
+    for (int e = 0; e < 16; ++e) v[e] = load(e * tpl);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) lb[lds_index<LS>(ts + e * tpl)] = v[e];
+    __syncthreads();
+  }
+#define FSEST_RT_FIRST(RR)                                                              \
+  case RR:                                                                              \
+    if (direct) rt_stage<RR, DIR, LS, SRC, STORE>(load, store, lb, ts, tpl, L, 1, tw);   \
+    else rt_stage<RR, DIR, LS, SRC, false>(load, store, lb, ts, tpl, L, 1, tw);          \
+    break;
+  switch (pl.radix[0]) {
+    case 16: break;
+    FSEST_RT_FIRST(15)
+    FSEST_RT_FIRST(12)
+    FSEST_RT_FIRST(10)
+    FSEST_RT_FIRST(9)
+    FSEST_RT_FIRST(8)
+    FSEST_RT_FIRST(6)
+    FSEST_RT_FIRST(4)
+    FSEST_RT_FIRST(2)
+    FSEST_RT_FIRST(3)
+    default: FSEST_RT_FIRST(5)
+  }
+#undef FSEST_RT_FIRST
+  int ns = via_lds ? 1 : pl.radix[0];
+  const int nmid = STORE ? nst - 1 : nst;
+  for (int s = via_lds ? 0 : 1; s < nmid; ++s) {
     const int r = pl.radix[s];
-    const uint32_t nsm = ns > 1 ? 0xFFFFFFFFu / (uint32_t)ns + 1u : 0u;
-    // the thread index passes through an empty asm statement in every stage,
-    // so that the compiler forms each stage's LDS addresses in that stage
-    // instead of hoisting those of every radix out of the loop (which spills)
-    int ts = t;
-    asm volatile("" : "+v"(ts));
+    asm volatile("" : "+v"(ts), "+s"(L), "+s"(tpl));
+#define FSEST_RT_MID(RR) \
+  case RR: rt_stage<RR, DIR, LS, kRtMid, false>(load, store, lb, ts, tpl, L, ns, tw); break;
     switch (r) {
-      case 16: rt_stage<16, DIR, LS>(lb, ts, tpl, L, ns, nsm, tw); break;
-      case 8: rt_stage<8, DIR, LS>(lb, ts, tpl, L, ns, nsm, tw); break;
-      case 4: rt_stage<4, DIR, LS>(lb, ts, tpl, L, ns, nsm, tw); break;
-      case 2: rt_stage<2, DIR, LS>(lb, ts, tpl, L, ns, nsm, tw); break;
-      case 3: rt_stage<3, DIR, LS>(lb, ts, tpl, L, ns, nsm, tw); break;
-      default: rt_stage<5, DIR, LS>(lb, ts, tpl, L, ns, nsm, tw); break;
+      case 16: rt_stage16<DIR, LS>(lb, ts, L, ns, tw); break;
+      FSEST_RT_MID(15)
+      FSEST_RT_MID(12)
+      FSEST_RT_MID(10)
+      FSEST_RT_MID(9)
+      FSEST_RT_MID(8)
+      FSEST_RT_MID(6)
+      FSEST_RT_MID(4)
+      FSEST_RT_MID(2)
+      FSEST_RT_MID(3)
+      default: FSEST_RT_MID(5)
     }
+#undef FSEST_RT_MID
     ns *= r;
   }
-  // elements past L are set to zero, not kept: their registers are then free
-  // during the stages
-#pragma unroll
-  for (int e = 0; e < 16; ++e)
-    v[e] = t + e * tpl < L ? lb[lds_index<LS>(t + e * tpl)] : make_float2(0.f, 0.f);
-  __syncthreads();
+  if constexpr (STORE) {
+    if (nst == 1) return;
+    asm volatile("" : "+v"(ts), "+s"(L), "+s"(tpl));
+    // the last radix holds the last factor 3 or 5 of the length
+#define FSEST_RT_LAST(RR) \
+  case RR: rt_stage<RR, DIR, LS, kRtMid, true>(load, store, lb, ts, tpl, L, ns, tw); break;
+    switch (pl.radix[nst - 1]) {
+      FSEST_RT_LAST(15)
+      FSEST_RT_LAST(12)
+      FSEST_RT_LAST(10)
+      FSEST_RT_LAST(9)
+      FSEST_RT_LAST(6)
+      FSEST_RT_LAST(3)
+      default: FSEST_RT_LAST(5)
+    }
+#undef FSEST_RT_LAST
+  }
 }
 
-// Plan for length L (host and device); false if L has a prime factor above 5.
+// Plan for length L (host and device); false if L has a prime factor above 5
+// or is a power of two above 8 (those have compile-time lines).
 __host__ __device__ inline bool make_rt_line(int L, RtLine* pl) {
   if (L < 2) return false;
   int rem = L, p2 = 1;
@@ -386,13 +548,21 @@ __host__ __device__ inline bool make_rt_line(int L, RtLine* pl) {
     r[nst++] = q;
     p2 /= q;
   }
+  if (rem == 1 && (nst > 1 || L > 8)) return false;
   while (rem % 3 == 0) { rem /= 3; r[nst++] = 3; }
   while (rem % 5 == 0) { rem /= 5; r[nst++] = 5; }
   if (rem != 1 || nst > kRtMaxStages) return false;
+  // neighbours whose product is a radix above, from the left
+  int n2 = 0;
+  for (int i = 0; i < nst; ++i) {
+    int q = r[i];
+    if (i + 1 < nst && q <= 4 && q * r[i + 1] <= 15 && !(q == 4 && r[i + 1] == 2)) q *= r[++i];
+    r[n2++] = q;
+  }
   pl->L = L;
   pl->tpl = (L + 15) / 16;
-  pl->nst = nst;
-  for (int i = 0; i < kRtMaxStages; ++i) pl->radix[i] = i < nst ? r[i] : 1;
+  pl->nst = n2;
+  for (int i = 0; i < kRtMaxStages; ++i) pl->radix[i] = i < n2 ? r[i] : 1;
   return true;
 }
 

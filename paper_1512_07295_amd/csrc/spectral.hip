@@ -212,20 +212,23 @@ __global__ __launch_bounds__(PairShape<L>::THREADS) void k_pairs(
     const bool self = (xa == xb) && (ya == yb);
     const int xr = r ? xb : xa, yr = r ? yb : ya;
     float2* gp = data + ((int64_t)mock * n + xr) * g.ps + (int64_t)yr * LL;
-    float2 v[EPT];
-    static_for<0, EPT>([&](auto e) {
-      const int j = t + e * TPL;
-      v[e] = (valid && (P2 || j < LL)) ? gp[j] : make_float2(0.f, 0.f);
-    });
-    if constexpr (MODE != 1) {
-      if constexpr (P2) line_fft<L, -1, 1>(v, t, own_lds, tw);
-      else line_fft_rt<-1, 1>(v, t, own_lds, rt, tw);
+    if constexpr (!P2 && MODE != 1) {
+      // the transform leaves the row in LDS (pairs past the last one read row 0)
+      line_fft_rt_io<-1, 1, kRtLoad, false>([&](int u) { return gp[t + u]; },
+                                   [](int, float2) {}, t, own_lds, rt, tw);
+    } else {
+      float2 v[EPT];
+      static_for<0, EPT>([&](auto e) {
+        const int j = t + e * TPL;
+        v[e] = (valid && (P2 || j < LL)) ? gp[j] : make_float2(0.f, 0.f);
+      });
+      if constexpr (MODE != 1) line_fft<L, -1, 1>(v, t, own_lds, tw);
+      static_for<0, EPT>([&](auto e) {
+        const int j = t + e * TPL;
+        if (P2 || j < LL) own_lds[lds_index<1>(j)] = v[e];
+      });
+      __syncthreads();
     }
-    static_for<0, EPT>([&](auto e) {
-      const int j = t + e * TPL;
-      if (P2 || j < LL) own_lds[lds_index<1>(j)] = v[e];
-    });
-    __syncthreads();
 
     const int mxr = signed_freq(xr, n), myr = signed_freq(yr, n);
     if constexpr (MODE != 2) {
@@ -378,13 +381,23 @@ __global__ __launch_bounds__(PairShape<L>::THREADS) void k_pairs(
         out[e] = acc;
       });
       __syncthreads();
-      if constexpr (P2) line_fft<L, +1, 1>(out, t, own_lds, tw);
-      else line_fft_rt<+1, 1>(out, t, own_lds, rt, tw);
-      if (valid && !(r == 1 && self))
+      const bool keep = valid && !(r == 1 && self);
+      if constexpr (P2) {
+        line_fft<L, +1, 1>(out, t, own_lds, tw);
+        if (keep) static_for<0, EPT>([&](auto e) { gp[t + e * TPL] = out[e]; });
+      } else {
+        // to LDS in natural order, from where the first stage takes its inputs
         static_for<0, EPT>([&](auto e) {
           const int j = t + e * TPL;
-          if (P2 || j < LL) gp[j] = out[e];
+          if (j < LL) own_lds[lds_index<1>(j)] = out[e];
         });
+        __syncthreads();
+        line_fft_rt_io<+1, 1, kRtFirst, true>([](int) { return make_float2(0.f, 0.f); },
+                                              [&](int u, float2 v) {
+                                                if (keep) gp[t + u] = v;
+                                              },
+                                              t, own_lds, rt, tw);
+      }
       __syncthreads();
     }
   }
@@ -556,18 +569,15 @@ __global__ __launch_bounds__(1024) void k_multi_pairs(
       const int xr = (r & 1) ? xb : xa, yr = (r & 1) ? yb : ya;
       const float2* gp = data + complex_index(g, mock * g.npair + r / 2, xr, yr, 0);
       float2* own = rows + r * rowp;
-      float2 v[EPT];
+      if constexpr (P2) {
+        float2 v[EPT];
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        const int j = tr + e * TPL;
-        v[e] = (P2 || j < n) ? gp[j] : make_float2(0.f, 0.f);
-      }
-      if constexpr (P2) line_fft<(P2 ? L : 16), -1, 1>(v, tr, own, tw);
-      else line_fft_rt<-1, 1>(v, tr, own, rt, tw);
+        for (int e = 0; e < EPT; ++e) v[e] = gp[tr + e * TPL];
+        line_fft<(P2 ? L : 16), -1, 1>(v, tr, own, tw);
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        const int j = tr + e * TPL;
-        if (P2 || j < n) own[lds_index<1>(j)] = v[e];
+        for (int e = 0; e < EPT; ++e) own[lds_index<1>(tr + e * TPL)] = v[e];
+      } else {
+        line_fft_rt_io<-1, 1, kRtLoad, false>([&](int u) { return gp[tr + u]; }, [](int, float2) {}, tr, own, rt, tw);
       }
     } else {
       for (int idx = threadIdx.x; idx < nr * n; idx += blockDim.x) {
