@@ -35,6 +35,8 @@ __device__ __forceinline__ int shell_of(int m2, int n_dk) {
   return ((r / n_dk) + 1) >> 1;
 }
 
+__device__ __forceinline__ int shell_or_zero(int m2, int n_dk) { return m2 ? shell_of(m2, n_dk) : 0; }
+
 // Row pair q of one set: rows (x, y) and (-x, -y); q < N^2/2 + 2.
 __device__ __forceinline__ void pair_rows(int64_t q, int n, int& x, int& y) {
   const int h1 = n / 2 + 1;

@@ -74,7 +74,8 @@ struct PairShape<0> {
 __host__ __device__ inline int rt_pairs_per_block(int tpl) { return 128 / tpl > 0 ? 128 / tpl : 1; }
 
 // MODE 0: forward z FFT + P(k) shell sums; MODE 1: shell sums of a stored
-// spectrum; MODE 2: forward z FFT, adjoint spectrum, inverse z FFT, write.
+// spectrum; MODE 2: forward z FFT, adjoint spectrum in place in LDS, inverse
+// z FFT, write.
 template <int L, bool IL, int MODE>
 __global__ __launch_bounds__(PairShape<L>::THREADS) void k_pairs(
     float2* __restrict__ data, Geom g, const float2* __restrict__ tw,
@@ -108,6 +109,8 @@ __global__ __launch_bounds__(PairShape<L>::THREADS) void k_pairs(
   constexpr int kCols = MODE != 2 ? kMaxBins + 2 : 1;
   __shared__ int colpre[kCols];
   __shared__ int coly[kCols];
+  // adjoint: the shells' coefficients
+  __shared__ float cff[MODE == 2 ? kMaxBins : 1];
 
   const int n = g.n;
   const int mock = blockIdx.y;
@@ -183,6 +186,10 @@ __global__ __launch_bounds__(PairShape<L>::THREADS) void k_pairs(
     }
     __syncthreads();
     npairs = colpre[n / 2 + 1];
+  }
+  if constexpr (MODE == 2) {
+    for (int i = threadIdx.x; i < n_bins; i += blockDim.x) cff[i] = (float)coef[(int64_t)mock * n_bins + i];
+    __syncthreads();
   }
   const int64_t ngroups = (npairs + PPB - 1) / PPB;
 
@@ -294,104 +301,120 @@ __global__ __launch_bounds__(PairShape<L>::THREADS) void k_pairs(
       }
       __syncthreads();
     } else {
-      // gradient of the loss with respect to Z at this thread's elements
-      const double* cf = coef + (int64_t)mock * n_bins;
-      const int xp = r ? xa : xb, yp = r ? ya : yb;  // partner row
-      const int mxp = signed_freq(xp, n), myp = signed_freq(yp, n);
-      float2 out[EPT];
-      static_for<0, EPT>([&](auto e) {
-        const int j = t + e * TPL;
-        float2 acc = make_float2(0.f, 0.f);
-        if (valid) {
+      // Gradient of the loss with respect to Z, in place in LDS: a half-space
+      // mode (row, mz) is built from Z(m) = row[mz] and Z(-m) = partner[-mz] and
+      // gives gradients to these two elements only, so the thread that takes
+      // the mode reads and writes them alone.
+      // Taking each mode once, instead of once per element that it touches,
+      // halves the arithmetic of this issue-bound pass, and without the line's
+      // elements in registers beside it a thread needs 159 VGPRs, not 246
+      // (row length 256).  Adjoint z pass, before -> after: N = 256 interlaced
+      // 114 -> 75 us, N = 64 20 -> 16 us, N = 240 interlaced 329 -> 102 us and
+      // not interlaced 106 -> 73 us, N = 100 58 -> 31 us.
+      float2* par = rows + (2 * ps + (r ^ 1)) * ROWP;
+      if (valid) {
+        // mode (mx, my, mz) of the row at (x, y) from its pair of elements: the
+        // gradients dZ(m) and dZ(-m); b is its shell
+        auto mode_grad = [&](int x, int y, int mx, int my, int mz, int b, float2 z1, float2 z2, float2& g1,
+                             float2& g2) __attribute__((always_inline)) {
+          g1 = g2 = make_float2(0.f, 0.f);
+          if (b < 1 || b > n_bins) return;
+          const float wgt = (mz == 0 || mz == n / 2) ? 1.0f : 2.0f;
+          const float s = wgt * cff[b - 1] * inv_w2[x] * inv_w2[y] * inv_w2[mz];
           if constexpr (IL) {
-            const float2 z1 = (P2 || j < LL) ? own_lds[lds_index<1>(j)] : make_float2(0.f, 0.f);
-            const float2 z2 = (P2 || j < LL) ? par_lds[lds_index<1>(neg_mod<P2>(j, n))] : make_float2(0.f, 0.f);
-            // (a) mode (own row, j) holds Z(m) = z1
-            if (j <= n / 2) {
-              const int m2 = mxr * mxr + myr * myr + j * j;
-              const int b = m2 ? shell_of(m2, n_dk) : 0;
-              if (b >= 1 && b <= n_bins) {
-                const float2 c = combined_mode<true, P2>(z1, z2, mxr, myr, j, phase, n);
-                const float wgt = (j == 0 || j == n / 2) ? 1.0f : 2.0f;
-                const float s = wgt * (float)cf[b - 1] * inv_w2[xr] * inv_w2[yr] * inv_w2[j];
-                const float2 gc = cscale(c, s);
-                const float2 ph = cconj(phase[mod_2n<P2>(mxr + myr + j, n)]);
-                const float2 gf1 = cscale(gc, 0.5f);
-                const float2 gf2 = cscale(cmul(ph, gc), 0.5f);
-                // dZ(m): 1/2 gF1 + (i/2) gF2
-                acc = cadd(acc, make_float2(0.5f * (gf1.x - gf2.y), 0.5f * (gf1.y + gf2.x)));
-              }
-            }
-            // (b) mode (partner row, -j) holds Z(-m') = z1
-            const int jp = neg_mod<P2>(j, n);
-            if ((P2 || j < LL) && jp <= n / 2) {
-              const int m2 = mxp * mxp + myp * myp + jp * jp;
-              const int b = m2 ? shell_of(m2, n_dk) : 0;
-              if (b >= 1 && b <= n_bins) {
-                const float2 c = combined_mode<true, P2>(z2, z1, mxp, myp, jp, phase, n);
-                const float wgt = (jp == 0 || jp == n / 2) ? 1.0f : 2.0f;
-                const float s = wgt * (float)cf[b - 1] * inv_w2[xp] * inv_w2[yp] * inv_w2[jp];
-                const float2 gc = cscale(c, s);
-                const float2 ph = cconj(phase[mod_2n<P2>(mxp + myp + jp, n)]);
-                const float2 gf1 = cscale(gc, 0.5f);
-                const float2 gf2 = cscale(cmul(ph, gc), 0.5f);
-                // dZ(-m'): 1/2 conj(gF1) + (i/2) conj(gF2)
-                acc = cadd(acc, make_float2(0.5f * (gf1.x + gf2.y), 0.5f * (-gf1.y + gf2.x)));
-              }
-            }
+            const float2 c = combined_mode<true, P2>(z1, z2, mx, my, mz, phase, n);
+            const float2 gc = cscale(c, s);
+            const float2 ph = cconj(phase[mod_2n<P2>(mx + my + mz, n)]);
+            const float2 gf1 = cscale(gc, 0.5f);
+            const float2 gf2 = cscale(cmul(ph, gc), 0.5f);
+            // dZ(m): 1/2 gF1 + (i/2) gF2; dZ(-m): 1/2 conj(gF1) + (i/2) conj(gF2)
+            g1 = make_float2(0.5f * (gf1.x - gf2.y), 0.5f * (gf1.y + gf2.x));
+            g2 = make_float2(0.5f * (gf1.x + gf2.y), 0.5f * (-gf1.y + gf2.x));
           } else {
-            const int h = n / 2;
-            const bool inl = P2 || j < LL;
-            const float2 z1 = inl ? own_lds[lds_index<1>(j)] : make_float2(0.f, 0.f);
-            const float2 z2 = inl ? par_lds[lds_index<1>(neg_mod<P2>(j, h))] : make_float2(0.f, 0.f);
-            // direct sources: modes (own row, mz) with mz = j (and mz = h when j = 0)
-            for (int k = 0; k < (!inl ? 0 : (j == 0) ? 2 : 1); ++k) {
-              const int mz = k ? h : j;
-              const int m2 = mxr * mxr + myr * myr + mz * mz;
-              const int b = m2 ? shell_of(m2, n_dk) : 0;
-              if (b >= 1 && b <= n_bins) {
-                const float2 c = combined_mode<false, P2>(z1, z2, mxr, myr, mz, phase, n);
-                const float wgt = (mz == 0 || mz == h) ? 1.0f : 2.0f;
-                const float s = wgt * (float)cf[b - 1] * inv_w2[xr] * inv_w2[yr] * inv_w2[mz];
-                const float2 gf = cscale(c, s);
-                const float2 ph = phase[mod_2n<P2>(2 * mz, n)];  // (cos, sin) of 2 pi mz/N
-                // conj(a) = ((1 - sin), cos) / 2
-                const float2 ca = make_float2(0.5f * (1.0f - ph.y), 0.5f * ph.x);
-                acc = cadd(acc, cmul(ca, gf));
+            const float2 c = combined_mode<false, P2>(z1, z2, mx, my, mz, phase, n);
+            const float2 gf = cscale(c, s);
+            const float2 ph = phase[mod_2n<P2>(2 * mz, n)];  // (cos, sin) of 2 pi mz/N
+            // conj(a) = ((1 - sin), cos) / 2 and b = ((1 + sin), cos) / 2
+            g1 = cmul(make_float2(0.5f * (1.0f - ph.y), 0.5f * ph.x), gf);
+            g2 = cmul(make_float2(0.5f * (1.0f + ph.y), 0.5f * ph.x), cconj(gf));
+          }
+        };
+        const int r2xy = mxr * mxr + myr * myr;  // the same for the partner row
+        const int xp = r ? xa : xb, yp = r ? ya : yb;
+        const int mxp = signed_freq(xp, n), myp = signed_freq(yp, n);
+        const int h = n / 2;
+        // both modes of a pair of elements at the same index e (0, and N/2 of
+        // interlaced rows), or of element e and its mirror f: own[e], par[f]
+        auto both = [&](int e, int f, int mz_own, int mz_par) __attribute__((always_inline)) {
+          const float2 z1 = own_lds[lds_index<1>(e)], z2 = par[lds_index<1>(f)];
+          const int b1 = shell_or_zero(r2xy + mz_own * mz_own, n_dk);
+          const int b2 = shell_or_zero(r2xy + mz_par * mz_par, n_dk);
+          float2 d1, e1, d2, e2;
+          mode_grad(xr, yr, mxr, myr, mz_own, b1, z1, z2, d1, e1);
+          mode_grad(xp, yp, mxp, myp, mz_par, b2, z2, z1, d2, e2);
+          float2 o1 = d1, o2 = d2;
+          if (!IL && mz_own == 0) {  // the packed plane mz = N/2 folds onto element 0
+            float2 d3, e3, d4, e4;
+            const int b3 = shell_or_zero(r2xy + h * h, n_dk);
+            mode_grad(xr, yr, mxr, myr, h, b3, z1, z2, d3, e3);
+            mode_grad(xp, yp, mxp, myp, h, b3, z2, z1, d4, e4);
+            o1 = cadd(o1, d3);
+            o2 = cadd(o2, d4);
+            e1 = cadd(e1, e3);
+            e2 = cadd(e2, e4);
+          }
+          own_lds[lds_index<1>(e)] = cadd(o1, e2);
+          par[lds_index<1>(f)] = cadd(o2, e1);
+        };
+        if constexpr (IL) {
+          // modes (own row, mz) of 0 < mz < N/2, a run per thread, the shell
+          // advancing along it (as in the shell sums)
+          const int per = (h - 1 + TPL - 1) / TPL;
+          const int z0 = 1 + t * per, z1e = min(z0 + per, h);
+          if (z0 < z1e) {
+            int m2 = r2xy + z0 * z0;
+            int b = shell_of(m2, n_dk);
+            const int nd2 = n_dk * n_dk;
+            int edge = (2 * b + 1) * n_dk;
+            edge *= edge;
+            int dedge = 8 * (b + 1) * nd2;
+            for (int mz = z0; mz < z1e; m2 += 2 * mz + 1, ++mz) {
+              while (edge <= 4 * m2) {
+                ++b;
+                edge += dedge;
+                dedge += 8 * nd2;
               }
-            }
-            // conjugate sources: modes (partner row, mz') with -mz' = j mod h (and h when j = 0)
-            for (int k = 0; k < (!inl ? 0 : (j == 0) ? 2 : 1); ++k) {
-              const int mz = k ? h : neg_mod<P2>(j, h);
-              const int m2 = mxp * mxp + myp * myp + mz * mz;
-              const int b = m2 ? shell_of(m2, n_dk) : 0;
-              if (b >= 1 && b <= n_bins) {
-                const float2 c = combined_mode<false, P2>(z2, z1, mxp, myp, mz, phase, n);
-                const float wgt = (mz == 0 || mz == h) ? 1.0f : 2.0f;
-                const float s = wgt * (float)cf[b - 1] * inv_w2[xp] * inv_w2[yp] * inv_w2[mz];
-                const float2 gf = cscale(c, s);
-                const float2 ph = phase[mod_2n<P2>(2 * mz, n)];
-                // b = ((1 + sin), cos) / 2
-                const float2 bb = make_float2(0.5f * (1.0f + ph.y), 0.5f * ph.x);
-                acc = cadd(acc, cmul(bb, cconj(gf)));
-              }
+              float2* e1 = own_lds + lds_index<1>(mz);
+              float2* e2 = par + lds_index<1>(n - mz);
+              float2 g1, g2;
+              mode_grad(xr, yr, mxr, myr, mz, b, *e1, *e2, g1, g2);
+              *e1 = g1;
+              *e2 = g2;
             }
           }
+          if (t == 0) {
+            const int e = r ? h : 0;  // row 0 takes element 0 of both rows, row 1 element N/2
+            both(e, e, e, e);
+          }
+        } else {
+          // elements own[j] and par[-j]: modes (own row, j) and (partner row, h - j)
+          // of 0 < j < h, and j = 0 with the planes mz = 0 and N/2; j shared by the rows
+          for (int j = 2 * t + r; j < h; j += 2 * TPL) {
+            // row 1 takes its j's as row 0 would: the same pairs, each once
+            if (r == 0) both(j, j ? h - j : 0, j, j ? h - j : 0);
+            else both(j ? h - j : 0, j, j ? h - j : 0, j);
+          }
         }
-        out[e] = acc;
-      });
+      }
       __syncthreads();
       const bool keep = valid && !(r == 1 && self);
       if constexpr (P2) {
+        float2 out[EPT];
+        static_for<0, EPT>([&](auto e) { out[e] = own_lds[lds_index<1>(t + e * TPL)]; });
+        __syncthreads();
         line_fft<L, +1, 1>(out, t, own_lds, tw);
         if (keep) static_for<0, EPT>([&](auto e) { gp[t + e * TPL] = out[e]; });
       } else {
-        // to LDS in natural order, from where the first stage takes its inputs
-        static_for<0, EPT>([&](auto e) {
-          const int j = t + e * TPL;
-          if (j < LL) own_lds[lds_index<1>(j)] = out[e];
-        });
-        __syncthreads();
         line_fft_rt_io<+1, 1, kRtFirst, true>([](int) { return make_float2(0.f, 0.f); },
                                               [&](int u, float2 v) {
                                                 if (keep) gp[t + u] = v;
