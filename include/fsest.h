@@ -65,7 +65,8 @@ typedef enum { EST_F32 = 0, EST_F64 = 1 } est_dtype;
 /* est_config.flags.  Particles are bucket-sorted (4^3-cell buckets) before
  * the deposit.  By default the sort works in two levels without
  * device-scope atomics: per-workgroup histograms over super-buckets of
- * up to 16^3 buckets (the edge is the largest divisor of N/4 up to 16),
+ * up to 16^3 buckets (the edge is a divisor of N/4, chosen by the particle
+ * capacity),
  * then one workgroup per super-bucket.  That workgroup count
  * bounds the second level, so for strongly clustered inputs (a large
  * fraction of all particles inside one super-bucket) this flag selects
@@ -201,10 +202,10 @@ est_status estimator_graph_capture(est_handle h, const void* pos,
 est_status estimator_graph_launch(est_handle h);
 
 /* Pick this handle's launch shapes (strided-FFT lines per workgroup, P(k)
- * reduction workgroups, deposit workgroup size, deposit work grouped per
- * XCD) by timing the whole pipeline on the given input `iters` times per
- * candidate, one parameter at a time.  The 32-bit fixed-point deposit stays
- * selected (it runs only where provably safe); estimator_set_launch can
+ * reduction workgroups, and of the general deposit kernel, which runs for
+ * orders 5 and 6 and N <= 16, the workgroup size and grouping per XCD) by
+ * timing the whole pipeline on the given input `iters` times per candidate,
+ * one parameter at a time.  The 32-bit fixed-point deposit stays selected (it runs only where provably safe); estimator_set_launch can
  * force the 64-bit one.  Returns the chosen combination as an index in
  * [0, 48) in *choice.  Results do not depend on the choice beyond rounding.
  * Host-synchronising. */
@@ -215,9 +216,8 @@ est_status estimator_autotune(est_handle h, const void* pos, est_dtype dtype,
 
 /* Set the launch shapes directly from an index returned by
  * estimator_autotune (e.g. one cached from an earlier run).  EINVAL outside
- * [0, 48).  Until a handle's shapes are set or tuned, its deposit workgroup
- * size is chosen per kernel (1024 threads where two such workgroups fit on
- * a CU, else 512). */
+ * [0, 48).  Until a handle's shapes are set or tuned, the P(k) reduction
+ * has as many workgroups as the device holds at once. */
 est_status estimator_set_launch(est_handle h, int32_t choice);
 
 /* Per-particle masses (the paper takes equal masses for simplicity,

@@ -108,9 +108,9 @@ struct Buffers {
 struct Tune {
   int cols_c = 16;        // lines per workgroup of the strided FFT passes
   int bin_blocks = 0;     // reduction workgroups per set in the fused P(k) pass (0: by occupancy)
-  int dep_threads = 0;    // threads per deposit workgroup (0: chosen per kernel)
+  int dep_threads = 0;    // threads per workgroup of the general deposit kernel (0: 512)
   int dep_narrow = 1;     // 32-bit fixed point when provably safe (else 64-bit)
-  int dep_xcd = 1;        // consecutive deposit tiles on one XCD (shared L2)
+  int dep_xcd = 1;        // its consecutive tiles on one XCD (shared L2)
   int cus = 256;          // compute units of the handle's device (set at create)
 };
 
