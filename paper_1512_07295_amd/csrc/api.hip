@@ -169,6 +169,18 @@ Geom make_geom(const est_config& c) {
   g.il = c.interlace ? 1 : 0;
   g.batch = c.batch;
   g.nb = c.n_grid / kBucket;
+  // The deposit walks columns of 16 x 16 x 8 tiles for orders 1..4 on grids
+  // larger than a tile (PCS pair, 1024^3 with 2^27 particles: 5.73 against 6.41
+  // ms).  Orders 1 and 2 on sparse grids stay with the general kernel, whose
+  // 16^3 tiles halve the work per tile that is all there is: with one particle
+  // in eight cells NGP pair 1024^3 3.89 against 4.91 ms and 512^3 0.53 against
+  // 0.62, CIC pair 4.25 against 4.87 (one CIC grid 3.33 and 3.43, 0.45 and
+  // 0.42 at 512^3); with one per cell the walk is faster
+  // (256^3: NGP pair 0.21 against 0.25 ms, CIC 0.24 against 0.31).  Their
+  // 64-bit format walks too (clustered NGP pair 512^3 0.75 against 0.97 ms).
+  g.walk = c.order <= 4 && c.n_grid > kTileMax &&
+           (c.order > (c.interlace ? 2 : 1) || c.n_grid < 256 ||
+            4 * c.max_particles >= (int64_t)c.batch * c.n_grid * c.n_grid * c.n_grid);
   // Super-bucket edge fb: a divisor of nb up to kFineMax, so super-buckets
   // tile the axis, and long enough that a deposit run in z meets at most one
   // super-bucket edge: 2 for the runs of up to 3 buckets of the z-walking
@@ -183,7 +195,7 @@ Geom make_geom(const est_config& c) {
   // the bucket pass has workgroups (32768 particles on 64^3: sort 61 us with
   // two super-buckets, 25 with 64).  If none qualifies, the largest.
   {
-    const int least = c.order <= 4 && c.n_grid > kTileMax ? 2 : 5;
+    const int least = g.walk ? 2 : 5;
     int64_t target = c.max_particles / 512 < 512 ? c.max_particles / 512 : 512;
     if (target < c.max_particles / 4096) target = c.max_particles / 4096;
     if (target < 1) target = 1;

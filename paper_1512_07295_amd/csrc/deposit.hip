@@ -197,8 +197,15 @@ __device__ __forceinline__ void deposit_item(uint4 rec, int gi, const Geom& g, i
 // a separate instantiation so that the equal-mass kernel keeps its registers
 // IL: 0 one grid; 1 the interlaced pair (masks 0 and 7); 2 a pair of grids
 // with run-time masks (mask_a, mask_b) written to slab q of each set
+// 32-bit pairs of orders 1 and 2 on grids larger than a tile: capped at 64
+// VGPRs (no scratch), so that two workgroups of 1024 threads fit in a CU
 template <int P, int IL, bool WIDE, int WRAP, bool WT>
-__global__ __launch_bounds__(1024) void k_deposit(const uint4* __restrict__ recs,
+__host__ __device__ constexpr bool two_groups_per_cu() {
+  return P <= 2 && IL == 1 && !WIDE && !WT && WRAP != kPeriodic;
+}
+
+template <int P, int IL, bool WIDE, int WRAP, bool WT>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(two_groups_per_cu<P, IL, WIDE, WRAP, WT>() ? 8 : 1))) void k_deposit(const uint4* __restrict__ recs,
                                                   const uint32_t* __restrict__ boff,
                                                   const uint32_t* __restrict__ bcnt, float* grid,
                                                   Geom g, uint32_t* __restrict__ stats,
@@ -420,8 +427,9 @@ __global__ __launch_bounds__(1024) void k_deposit(const uint4* __restrict__ recs
       int rpar = 0;  // which of the three round counters this round uses
 
       // rounds of blockDim candidates; the cell records of kPre rounds are
-      // loaded together so that their latencies overlap
-      constexpr int kPre = 4;
+      // loaded together so that their latencies overlap (one round where the
+      // registers are capped: the other workgroup on the CU covers the wait)
+      constexpr int kPre = two_groups_per_cu<P, IL, WIDE, WRAP, WT>() ? 1 : 4;
       constexpr int off = (P % 2 == 0) ? (P / 2 - 1) : (P - 1) / 2;
       for (uint32_t rb = 0; rb < total; rb += kPre * nthreads) {
         uint32_t jj[kPre];
@@ -622,6 +630,7 @@ static void deposit_launch(const Geom& g, const Buffers& b, int threads, bool na
   // of a segment's first tile distinct from its own
   constexpr int kLow = (P - 1 + (IL ? 1 : 0) + kBucket - 1) / kBucket;
   const bool walk = WRAP != kPeriodic && g.n >= g.tile + kBucket * kLow;
+  constexpr bool kTwo = two_groups_per_cu<P, IL, false, WRAP, WT>();
   const int seg = walk ? walk_segment(g, cus) : 1;
   const int64_t nunits = (int64_t)g.batch * tpa * tpa * ((tpa + seg - 1) / seg);
   if (narrow) {
@@ -629,16 +638,18 @@ static void deposit_launch(const Geom& g, const Buffers& b, int threads, bool na
     // grouping), each looping over units
     const int64_t cap = (int64_t)cus * 8;
     const unsigned nwg = (unsigned)(nunits < cap ? nunits : cap);
-    hipLaunchKernelGGL((k_deposit<P, IL, false, WRAP, WT>), dim3(nwg), dim3(threads), 0, s,
+    hipLaunchKernelGGL((k_deposit<P, IL, false, WRAP, WT>), dim3(nwg),
+                       dim3(threads ? threads : kTwo ? 1024 : 512), 0, s,
                        (const uint4*)b.recs, b.boff, b.bcnt, (float*)b.grid, g, b.stats, 0, 0,
                        xcd ? 1 : 0, sw, q, ma, mb, walk ? 1 : 0, seg);
   }
+  if constexpr (P <= 4 && WRAP != kPeriodic) return;  // the walk's 64-bit kernel follows
   // the 64-bit kernel holds one workgroup per CU; it takes units from a
   // counter, so when the 32-bit kernel does the work it costs one short wave
   // per workgroup
   const unsigned wblocks = (unsigned)(nunits < 1024 ? nunits : 1024);
   hipLaunchKernelGGL((k_deposit<P, IL, true, WRAP, WT>), dim3(wblocks),
-                     dim3(threads), 0, s, (const uint4*)b.recs, b.boff, b.bcnt,
+                     dim3(threads ? threads : 512), 0, s, (const uint4*)b.recs, b.boff, b.bcnt,
                      (float*)b.grid, g, b.stats, narrow ? 0 : 1, 1, 0, sw, q, ma, mb,
                      walk ? 1 : 0, seg);
 }
@@ -659,15 +670,16 @@ static void dispatch_deposit_t(const Geom& g, const Buffers& b, const Tune& tu, 
     dispatch_deposit_w<P, IL, kPeriodic>(g, b, threads, narrow, xcd, tu.cus, sw, q, ma, mb, s);
     return;
   }
-  // orders 1..4 on larger grids walk smaller tiles with lighter work items:
-  // at 1024^3 with 2^27 particles (PCS pair) 5.73 ms against 6.41 ms here
-  if constexpr (P <= 4) {
-    (void)launch_deposit_walk(g, b, tu, sw, q, ma, mb, s);  // reported by launch_deposit
-  } else if ((g.n & (g.n - 1)) == 0) {
-    dispatch_deposit_w<P, IL, kMasked>(g, b, threads, narrow, xcd, tu.cus, sw, q, ma, mb, s);
-  } else {
-    dispatch_deposit_w<P, IL, kGeneral>(g, b, threads, narrow, xcd, tu.cus, sw, q, ma, mb, s);
+  // 32-bit format of orders 1 and 2 on sparse grids, both of orders 5 and 6
+  if constexpr (P <= 2 || P >= 5) {
+    if (P >= 5 || (!g.walk && narrow)) {
+      if ((g.n & (g.n - 1)) == 0)
+        dispatch_deposit_w<P, IL, kMasked>(g, b, threads, narrow, xcd, tu.cus, sw, q, ma, mb, s);
+      else
+        dispatch_deposit_w<P, IL, kGeneral>(g, b, threads, narrow, xcd, tu.cus, sw, q, ma, mb, s);
+    }
   }
+  if constexpr (P <= 4) (void)launch_deposit_walk(g, b, tu, sw, q, ma, mb, s);  // reported by launch_deposit
 }
 
 template <int P>
@@ -689,7 +701,7 @@ static void dispatch_deposit_p(const Geom& g, const Buffers& b, const Tune& tu, 
 
 hipError_t launch_deposit(const Geom& g, const Buffers& b, const Tune& tu, bool weighted,
                           hipStream_t s) {
-  const int threads = tu.dep_threads == 1024 ? 1024 : 512;
+  const int threads = tu.dep_threads;  // 0: chosen per kernel
   const float* sw = weighted ? b.sw : nullptr;
   switch (g.order) {
     case 1: dispatch_deposit_p<1>(g, b, tu, threads, sw, s); break;

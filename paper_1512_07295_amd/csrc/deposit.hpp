@@ -90,7 +90,8 @@ __device__ __forceinline__ int find_segment(const DepRanges& rg, int nr, uint32_
 }
 
 // The z-walking deposit (deposit_walk.hip): orders 1..4 on grids larger than
-// a tile.  q, ma, mb: slab and shift masks of interlacing codes 2 and 3.
+// a tile; where g.walk is not set the 64-bit format only.  q, ma, mb: slab and
+// shift masks of interlacing codes 2 and 3.
 hipError_t launch_deposit_walk(const Geom& g, const Buffers& b, const Tune& tu, const float* sw,
                                int q, int ma, int mb, hipStream_t s);
 

@@ -533,7 +533,7 @@ template <int P, int IL, bool POW2, bool WT>
 static void walk_formats(const Geom& g, const Buffers& b, const Tune& tu, const float* sw, int q,
                          int ma, int mb, hipStream_t s) {
   const bool narrow = tu.dep_narrow != 0;
-  if (narrow) walk_launch<P, IL, false, POW2, WT>(g, b, tu, false, sw, q, ma, mb, s);
+  if (narrow && g.walk) walk_launch<P, IL, false, POW2, WT>(g, b, tu, false, sw, q, ma, mb, s);
   walk_launch<P, IL, true, POW2, WT>(g, b, tu, !narrow, sw, q, ma, mb, s);
 }
 

@@ -40,6 +40,7 @@ struct Geom {
   int npair;      // complex grids (slabs) per set: max(1, ng / 2); slab = set * npair + q
   int batch;
   int nb;         // buckets per axis = N / kBucket
+  bool walk;      // the deposit walks columns of tiles (deposit_walk.hip)
   int tile;       // deposit tile edge
   int fb;         // buckets per super-bucket edge: min(kFineMax, nb)
   uint32_t fb_mul;  // floor(2^32 / fb) + 1 (fb >= 2): x / fb = umulhi(x, fb_mul) for x < 2^16
@@ -108,7 +109,7 @@ struct Buffers {
 struct Tune {
   int cols_c = 16;        // lines per workgroup of the strided FFT passes
   int bin_blocks = 0;     // reduction workgroups per set in the fused P(k) pass (0: by occupancy)
-  int dep_threads = 0;    // threads per workgroup of the general deposit kernel (0: 512)
+  int dep_threads = 0;    // threads per workgroup of the general deposit kernel (0: chosen per kernel)
   int dep_narrow = 1;     // 32-bit fixed point when provably safe (else 64-bit)
   int dep_xcd = 1;        // its consecutive tiles on one XCD (shared L2)
   int cus = 256;          // compute units of the handle's device (set at create)
