@@ -35,13 +35,14 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 # the traffic as unknown (null).
 MEASURED_TRAFFIC = {
     "deposit": {
-        "sources": ["paper_1512_07295_amd/csrc/deposit.hip",
+        "sources": ["paper_1512_07295_amd/csrc/deposit_walk.hip",
+                    "paper_1512_07295_amd/csrc/deposit.hpp",
                     "paper_1512_07295_amd/csrc/particles.hpp",
                     "paper_1512_07295_amd/csrc/fsest_internal.hpp"],
-        "sha256_16": "ed4bfdfd521b6dbe",
+        "sha256_16": "be641659488569d7",
         "workload": "pcs_il_n1024_za512",
-        "read_bytes": 2 * 1835244 * 1024,
-        "write_bytes": 8388618 * 1024,
+        "read_bytes": 2 * 3016336 * 1024,
+        "write_bytes": 10429010 * 1024,
     },
 }
 

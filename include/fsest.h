@@ -203,7 +203,8 @@ est_status estimator_graph_launch(est_handle h);
 
 /* Pick this handle's launch shapes (strided-FFT lines per workgroup, P(k)
  * reduction workgroups, and of the general deposit kernel, which runs for
- * orders 5 and 6 and N <= 16, the workgroup size and grouping per XCD) by
+ * orders 5 and 6, N <= 16 and low orders on sparse grids, the workgroup size
+ * and grouping per XCD) by
  * timing the whole pipeline on the given input `iters` times per candidate,
  * one parameter at a time.  The 32-bit fixed-point deposit stays selected (it runs only where provably safe); estimator_set_launch can
  * force the 64-bit one.  Returns the chosen combination as an index in
