@@ -623,8 +623,8 @@ static int walk_segment(const Geom& g, int cus) {
 }
 
 template <int P, int IL, int WRAP, bool WT>
-static void deposit_launch(const Geom& g, const Buffers& b, int threads, bool narrow, bool xcd,
-                           int cus, const float* sw, int q, int ma, int mb, hipStream_t s) {
+static hipError_t deposit_launch(const Geom& g, const Buffers& b, int threads, bool narrow, bool xcd,
+                                 int cus, const float* sw, int q, int ma, int mb, hipStream_t s) {
   const int tpa = (g.n + g.tile - 1) / g.tile;
   // the z walk needs a tile smaller than the grid and the look-back buckets
   // of a segment's first tile distinct from its own
@@ -642,8 +642,10 @@ static void deposit_launch(const Geom& g, const Buffers& b, int threads, bool na
                        dim3(threads ? threads : kTwo ? 1024 : 512), 0, s,
                        (const uint4*)b.recs, b.boff, b.bcnt, (float*)b.grid, g, b.stats, 0, 0,
                        xcd ? 1 : 0, sw, q, ma, mb, walk ? 1 : 0, seg);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
-  if constexpr (P <= 4 && WRAP != kPeriodic) return;  // the walk's 64-bit kernel follows
+  if constexpr (P <= 4 && WRAP != kPeriodic) return hipSuccess;  // the walk's 64-bit kernel follows
   // the 64-bit kernel holds one workgroup per CU; it takes units from a
   // counter, so when the 32-bit kernel does the work it costs one short wave
   // per workgroup
@@ -652,51 +654,50 @@ static void deposit_launch(const Geom& g, const Buffers& b, int threads, bool na
                      dim3(threads ? threads : 512), 0, s, (const uint4*)b.recs, b.boff, b.bcnt,
                      (float*)b.grid, g, b.stats, narrow ? 0 : 1, 1, 0, sw, q, ma, mb,
                      walk ? 1 : 0, seg);
+  return hipGetLastError();
 }
 
 template <int P, int IL, int WRAP>
-static void dispatch_deposit_w(const Geom& g, const Buffers& b, int threads, bool narrow, bool xcd,
-                               int cus, const float* sw, int q, int ma, int mb, hipStream_t s) {
-  if (sw) deposit_launch<P, IL, WRAP, true>(g, b, threads, narrow, xcd, cus, sw, q, ma, mb, s);
-  else deposit_launch<P, IL, WRAP, false>(g, b, threads, narrow, xcd, cus, nullptr, q, ma, mb, s);
+static hipError_t dispatch_deposit_w(const Geom& g, const Buffers& b, int threads, bool narrow, bool xcd,
+                                     int cus, const float* sw, int q, int ma, int mb, hipStream_t s) {
+  return sw ? deposit_launch<P, IL, WRAP, true>(g, b, threads, narrow, xcd, cus, sw, q, ma, mb, s)
+            : deposit_launch<P, IL, WRAP, false>(g, b, threads, narrow, xcd, cus, nullptr, q, ma, mb, s);
 }
 
 template <int P, int IL>
-static void dispatch_deposit_t(const Geom& g, const Buffers& b, const Tune& tu, int threads,
-                               const float* sw, int q, int ma, int mb, hipStream_t s) {
+static hipError_t dispatch_deposit_t(const Geom& g, const Buffers& b, const Tune& tu, int threads,
+                                     const float* sw, int q, int ma, int mb, hipStream_t s) {
   const bool narrow = tu.dep_narrow != 0;
   const bool xcd = tu.dep_xcd != 0;
-  if (g.tile == g.n) {
-    dispatch_deposit_w<P, IL, kPeriodic>(g, b, threads, narrow, xcd, tu.cus, sw, q, ma, mb, s);
-    return;
-  }
+  if (g.tile == g.n)
+    return dispatch_deposit_w<P, IL, kPeriodic>(g, b, threads, narrow, xcd, tu.cus, sw, q, ma, mb, s);
   // 32-bit format of orders 1 and 2 on sparse grids, both of orders 5 and 6
   if constexpr (P <= 2 || P >= 5) {
     if (P >= 5 || (!g.walk && narrow)) {
-      if ((g.n & (g.n - 1)) == 0)
-        dispatch_deposit_w<P, IL, kMasked>(g, b, threads, narrow, xcd, tu.cus, sw, q, ma, mb, s);
-      else
-        dispatch_deposit_w<P, IL, kGeneral>(g, b, threads, narrow, xcd, tu.cus, sw, q, ma, mb, s);
+      const hipError_t e =
+          (g.n & (g.n - 1)) == 0
+              ? dispatch_deposit_w<P, IL, kMasked>(g, b, threads, narrow, xcd, tu.cus, sw, q, ma, mb, s)
+              : dispatch_deposit_w<P, IL, kGeneral>(g, b, threads, narrow, xcd, tu.cus, sw, q, ma, mb, s);
+      if (P >= 5 || e != hipSuccess) return e;
     }
   }
-  if constexpr (P <= 4) (void)launch_deposit_walk(g, b, tu, sw, q, ma, mb, s);  // reported by launch_deposit
+  return launch_deposit_walk(g, b, tu, sw, q, ma, mb, s);
 }
 
 template <int P>
-static void dispatch_deposit_p(const Geom& g, const Buffers& b, const Tune& tu, int threads,
-                               const float* sw, hipStream_t s) {
-  if (g.code == 0) {
-    dispatch_deposit_t<P, 0>(g, b, tu, threads, sw, 0, 0, 0, s);
-  } else if (g.code == 1) {
-    dispatch_deposit_t<P, 1>(g, b, tu, threads, sw, 0, 0, 7, s);
-  } else {
-    // one pass per slab; the 64-bit kernel's tile counter restarts each time
-    for (int q = 0; q < g.npair; ++q) {
-      if (q > 0) (void)launch_fill_u32(b.stats + 1, 1, 0u, s);  // reported by launch_deposit
-      dispatch_deposit_t<P, 2>(g, b, tu, threads, sw, q, grid_mask(g.code, 2 * q),
-                               grid_mask(g.code, 2 * q + 1), s);
-    }
+static hipError_t dispatch_deposit_p(const Geom& g, const Buffers& b, const Tune& tu, int threads,
+                                     const float* sw, hipStream_t s) {
+  if (g.code == 0) return dispatch_deposit_t<P, 0>(g, b, tu, threads, sw, 0, 0, 0, s);
+  if (g.code == 1) return dispatch_deposit_t<P, 1>(g, b, tu, threads, sw, 0, 0, 7, s);
+  // one pass per slab; the unit counter restarts each time
+  for (int q = 0; q < g.npair; ++q) {
+    hipError_t e = q > 0 ? launch_fill_u32(b.stats + 1, 1, 0u, s) : hipSuccess;
+    if (e == hipSuccess)
+      e = dispatch_deposit_t<P, 2>(g, b, tu, threads, sw, q, grid_mask(g.code, 2 * q),
+                                   grid_mask(g.code, 2 * q + 1), s);
+    if (e != hipSuccess) return e;
   }
+  return hipSuccess;
 }
 
 hipError_t launch_deposit(const Geom& g, const Buffers& b, const Tune& tu, bool weighted,
@@ -704,14 +705,13 @@ hipError_t launch_deposit(const Geom& g, const Buffers& b, const Tune& tu, bool 
   const int threads = tu.dep_threads;  // 0: chosen per kernel
   const float* sw = weighted ? b.sw : nullptr;
   switch (g.order) {
-    case 1: dispatch_deposit_p<1>(g, b, tu, threads, sw, s); break;
-    case 2: dispatch_deposit_p<2>(g, b, tu, threads, sw, s); break;
-    case 3: dispatch_deposit_p<3>(g, b, tu, threads, sw, s); break;
-    case 4: dispatch_deposit_p<4>(g, b, tu, threads, sw, s); break;
-    case 5: dispatch_deposit_p<5>(g, b, tu, threads, sw, s); break;
-    default: dispatch_deposit_p<6>(g, b, tu, threads, sw, s); break;
+    case 1: return dispatch_deposit_p<1>(g, b, tu, threads, sw, s);
+    case 2: return dispatch_deposit_p<2>(g, b, tu, threads, sw, s);
+    case 3: return dispatch_deposit_p<3>(g, b, tu, threads, sw, s);
+    case 4: return dispatch_deposit_p<4>(g, b, tu, threads, sw, s);
+    case 5: return dispatch_deposit_p<5>(g, b, tu, threads, sw, s);
+    default: return dispatch_deposit_p<6>(g, b, tu, threads, sw, s);
   }
-  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ test hook

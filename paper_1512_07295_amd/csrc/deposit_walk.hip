@@ -517,8 +517,8 @@ static int walk_segment(const Geom& g, int64_t slots) {
 }
 
 template <int P, int IL, bool WIDE, bool POW2, bool WT>
-static void walk_launch(const Geom& g, const Buffers& b, const Tune& tu, bool exclusive,
-                        const float* sw, int q, int ma, int mb, hipStream_t s) {
+static hipError_t walk_launch(const Geom& g, const Buffers& b, const Tune& tu, bool exclusive,
+                              const float* sw, int q, int ma, int mb, hipStream_t s) {
   const int tpa = (g.n + kWalkT - 1) / kWalkT, tpz = (g.n + kWalkTZ - 1) / kWalkTZ;
   const int64_t slots = (int64_t)tu.cus * walk_groups_per_cu<IL, WIDE>();
   const int seg = walk_segment(g, slots);
@@ -528,47 +528,49 @@ static void walk_launch(const Geom& g, const Buffers& b, const Tune& tu, bool ex
                      dim3((unsigned)(dynamic ? slots : nunits)), dim3(kWalkThreads), 0, s,
                      (const uint4*)b.recs, b.boff, b.bcnt, (float*)b.grid, g, b.stats,
                      exclusive ? 1 : 0, dynamic ? 1 : 0, sw, q, ma, mb, seg);
+  return hipGetLastError();
 }
 
 template <int P, int IL, bool POW2, bool WT>
-static void walk_formats(const Geom& g, const Buffers& b, const Tune& tu, const float* sw, int q,
-                         int ma, int mb, hipStream_t s) {
+static hipError_t walk_formats(const Geom& g, const Buffers& b, const Tune& tu, const float* sw, int q,
+                               int ma, int mb, hipStream_t s) {
   const bool narrow = tu.dep_narrow != 0;
-  if (narrow && g.walk) walk_launch<P, IL, false, POW2, WT>(g, b, tu, false, sw, q, ma, mb, s);
-  walk_launch<P, IL, true, POW2, WT>(g, b, tu, !narrow, sw, q, ma, mb, s);
+  if (narrow && g.walk) {
+    const hipError_t e = walk_launch<P, IL, false, POW2, WT>(g, b, tu, false, sw, q, ma, mb, s);
+    if (e != hipSuccess) return e;
+  }
+  return walk_launch<P, IL, true, POW2, WT>(g, b, tu, !narrow, sw, q, ma, mb, s);
 }
 
 template <int P, int IL>
-static void walk_dispatch(const Geom& g, const Buffers& b, const Tune& tu, const float* sw, int q,
-                          int ma, int mb, hipStream_t s) {
+static hipError_t walk_dispatch(const Geom& g, const Buffers& b, const Tune& tu, const float* sw, int q,
+                                int ma, int mb, hipStream_t s) {
   const bool pow2 = (g.n & (g.n - 1)) == 0;
   if (pow2) {
-    if (sw) walk_formats<P, IL, true, true>(g, b, tu, sw, q, ma, mb, s);
-    else walk_formats<P, IL, true, false>(g, b, tu, sw, q, ma, mb, s);
-  } else {
-    if (sw) walk_formats<P, IL, false, true>(g, b, tu, sw, q, ma, mb, s);
-    else walk_formats<P, IL, false, false>(g, b, tu, sw, q, ma, mb, s);
+    return sw ? walk_formats<P, IL, true, true>(g, b, tu, sw, q, ma, mb, s)
+              : walk_formats<P, IL, true, false>(g, b, tu, sw, q, ma, mb, s);
   }
+  return sw ? walk_formats<P, IL, false, true>(g, b, tu, sw, q, ma, mb, s)
+            : walk_formats<P, IL, false, false>(g, b, tu, sw, q, ma, mb, s);
 }
 
 template <int P>
-static void walk_order(const Geom& g, const Buffers& b, const Tune& tu, const float* sw, int q,
-                       int ma, int mb, hipStream_t s) {
-  if (g.code == 0) walk_dispatch<P, 0>(g, b, tu, sw, q, ma, mb, s);
-  else if (g.code == 1) walk_dispatch<P, 1>(g, b, tu, sw, q, ma, mb, s);
-  else walk_dispatch<P, 2>(g, b, tu, sw, q, ma, mb, s);
+static hipError_t walk_order(const Geom& g, const Buffers& b, const Tune& tu, const float* sw, int q,
+                             int ma, int mb, hipStream_t s) {
+  if (g.code == 0) return walk_dispatch<P, 0>(g, b, tu, sw, q, ma, mb, s);
+  if (g.code == 1) return walk_dispatch<P, 1>(g, b, tu, sw, q, ma, mb, s);
+  return walk_dispatch<P, 2>(g, b, tu, sw, q, ma, mb, s);
 }
 
 hipError_t launch_deposit_walk(const Geom& g, const Buffers& b, const Tune& tu, const float* sw,
                                int q, int ma, int mb, hipStream_t s) {
   switch (g.order) {
-    case 1: walk_order<1>(g, b, tu, sw, q, ma, mb, s); break;
-    case 2: walk_order<2>(g, b, tu, sw, q, ma, mb, s); break;
-    case 3: walk_order<3>(g, b, tu, sw, q, ma, mb, s); break;
-    case 4: walk_order<4>(g, b, tu, sw, q, ma, mb, s); break;
+    case 1: return walk_order<1>(g, b, tu, sw, q, ma, mb, s);
+    case 2: return walk_order<2>(g, b, tu, sw, q, ma, mb, s);
+    case 3: return walk_order<3>(g, b, tu, sw, q, ma, mb, s);
+    case 4: return walk_order<4>(g, b, tu, sw, q, ma, mb, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 }  // namespace fsest
