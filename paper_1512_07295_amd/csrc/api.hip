@@ -236,16 +236,16 @@ size_t layout(const est_config& c, char* base, Buffers* b, void** tune_out) {
   Buffers bb;
   bb.grid = (float2*)take(batch * g.npair * n * (size_t)g.ps * sizeof(float2));
   bb.recs = (uint4*)take((size_t)c.max_particles * sizeof(uint4));
-  bb.rank = (uint32_t*)take((size_t)c.max_particles * sizeof(uint32_t));
+  const bool two_level = g.nsup <= kMaxSuper;
+  // ranks (atomic sort), or buckets inside the super-bucket
+  bb.rank = (uint32_t*)take((size_t)c.max_particles * (two_level ? sizeof(uint16_t) : sizeof(uint32_t)));
   bb.boff = (uint32_t*)take(nkeys * sizeof(uint32_t));
   bb.bcnt = (uint32_t*)take(nkeys * sizeof(uint32_t));
-  const bool two_level = g.nsup <= kMaxSuper;
   bb.trecs = two_level ? (uint4*)take((size_t)c.max_particles * sizeof(uint4)) : nullptr;
-  // block-major histograms (kMaxSortBlocks rows of nsup), the nsup + 1 super-bucket starts, nsup totals
-  const size_t nh = two_level ? (size_t)g.nsup * (kMaxSortBlocks + 2) + 1 : 0;
+  // block-major histograms (a row of nsup per workgroup), the nsup + 1 super-bucket starts, nsup totals
+  const size_t nh = (size_t)g.nsup * (sort_blocks(c.max_particles) + 2) + 1;
   bb.hsup = two_level ? (uint32_t*)take(nh * sizeof(uint32_t)) : nullptr;
-  const size_t nscan = nkeys > nh ? nkeys : nh;
-  bb.scan_tmp = (uint32_t*)take(((nscan + 2047) / 2048 + 1) * sizeof(uint32_t));
+  bb.scan_tmp = two_level ? nullptr : (uint32_t*)take(((nkeys + 2047) / 2048 + 1) * sizeof(uint32_t));
   bb.stats = (uint32_t*)take(64 * sizeof(uint32_t));
   bb.tw_n = (float2*)take(n * sizeof(float2));
   bb.tw_nz = (float2*)take((size_t)g.nz * sizeof(float2));
@@ -260,7 +260,9 @@ size_t layout(const est_config& c, char* base, Buffers* b, void** tune_out) {
   const bool weighted = (c.flags & EST_FLAG_WEIGHTS) != 0;
   bb.sw = weighted ? (float*)take((size_t)c.max_particles * sizeof(float)) : nullptr;
   bb.tw = weighted && two_level ? (float*)take((size_t)c.max_particles * sizeof(float)) : nullptr;
-  bb.wpart = weighted ? (double*)take(batch * weight_slices(c.batch) * kWPartDoubles * sizeof(double)) : nullptr;
+  // (a set's 2048 rows of N/2 >= 4 sums hold its at most 1024 slices)
+  static_assert(kMaxBinBlocks * 4 * sizeof(double) >= kWSlicesMax * kWPartBytes, "mass sums fit in the partial sums");
+  bb.wpart = weighted ? bb.partials : nullptr;
   bb.cbuf = c.interlace >= 2 ? (float2*)take(batch * n * n * (half + 1) * sizeof(float2)) : nullptr;
   bb.coef = (double*)take(batch * half * sizeof(double));
   bb.mode_partials_n = (uint64_t*)take(512 * half * sizeof(uint64_t));

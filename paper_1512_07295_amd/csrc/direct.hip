@@ -169,9 +169,15 @@ int direct_slices(int ngrid, int64_t n) {
   return (int)s;
 }
 
-// workspace: fixed-point phases, the mass sums (partials, totals, flags),
-// then the per-slice partial spectra
-constexpr size_t kDirMassBytes = 256 * ((kWPartDoubles * kWSlicesMax * 8 + 2 * 8 + 64 * 4 + 255) / 256);
+// workspace: fixed-point phases, the mass totals and flags with room for 1024
+// slices' float64 sums, then the per-slice partial spectra.  The slices' words
+// reach into the spectra's memory, which is written after they are read: the
+// size of a call's workspace, and with it what the static workspace accepts,
+// does not depend on them.
+constexpr size_t kDirMassBytes = 256 * ((2 * kWSlicesMax * 8 + 2 * 8 + 64 * 4 + 255) / 256);
+constexpr size_t kDirLeastSpectrum = 8 * 8 * 5 * 2 * sizeof(double);  // N = 8, one slice
+static_assert(2 * 8 + 64 * 4 + kWSlicesMax * kWPartBytes <= kDirMassBytes + kDirLeastSpectrum,
+              "the mass sums stay inside the workspace");
 
 // Static workspace of the allocation-free entry point.  In host code the
 // name `scratch` only stands for the symbol: its device address comes from
@@ -222,9 +228,9 @@ hipError_t launch_direct(const Geom& g, const void* pos, est_dtype dt, int64_t n
   const int nslices = direct_slices(ngrid, n);
   uint32_t* q = (uint32_t*)ws;
   char* mass = (char*)ws + ((size_t)n * 3 * sizeof(uint32_t) + 255) / 256 * 256;
-  double* wpart = (double*)mass;
-  double* norm = wpart + kWPartDoubles * kWSlicesMax;
+  double* norm = (double*)mass;
   uint32_t* stats = (uint32_t*)(norm + 2);
+  double* wpart = (double*)(stats + 64);
   double* partial = (double*)(mass + kDirMassBytes);
   if (w) {
     hipError_t e = launch_weight_stats(w, nullptr, n, 1, wpart, norm, stats, s);

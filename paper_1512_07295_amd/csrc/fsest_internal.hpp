@@ -25,8 +25,15 @@ __host__ __device__ inline int weight_slices(int batch) {
   return s < 16 ? 16 : (s > kWSlicesMax ? kWSlicesMax : s);
 }
 
-// doubles per slice of the mass-sum pass: sum w, sum w^2, (largest mass, flag)
-constexpr int kWPartDoubles = 3;
+// bytes that the mass-sum pass leaves per slice: sum w and sum w^2 (float64),
+// and, after those of every slice, the largest mass's bits or ~0 (invalid mass)
+constexpr size_t kWPartBytes = 2 * sizeof(double) + sizeof(uint32_t);
+
+// workgroups of the super-bucket passes for n particles
+__host__ __device__ inline int sort_blocks(int64_t n) {
+  const int64_t b = (n + 4095) / 4096;
+  return b < kMaxSortBlocks ? (int)b : kMaxSortBlocks;
+}
 
 // Geometry and per-call constants that device code needs.
 struct Geom {
@@ -79,9 +86,9 @@ struct Buffers {
   uint32_t* boff;          // batch * nb^3 + 1 bucket start offsets (key order)
   uint32_t* bcnt;          // batch * nb^3 bucket counts
   uint4* trecs;            // max_particles records in super-bucket order (two-level sort)
-  uint32_t* hsup;          // kMaxSortBlocks x nsup block-major histograms / offsets,
+  uint32_t* hsup;          // sort_blocks(n) x nsup block-major histograms / offsets,
                            // then the nsup + 1 super-bucket starts and the nsup totals
-  uint32_t* scan_tmp;      // scan block sums
+  uint32_t* scan_tmp;      // scan block sums (atomic sort)
   uint32_t* stats;         // [0] largest bucket count of the last sort, [1] tile counter,
                            // [4] largest mass (float bits), [5] nonzero if a mass is
                            // negative or not finite
@@ -98,7 +105,8 @@ struct Buffers {
                            // (N_P, N_P for equal masses)
   float* sw;               // max_particles masses / largest mass, bucket order (weighted handles)
   float* tw;               // max_particles masses in super-bucket order (weighted, two-level)
-  double* wpart;           // batch x weight_slices(batch) x kWPartDoubles partial mass sums (weighted)
+  double* wpart;           // batch x weight_slices(batch) x kWPartBytes of mass sums (weighted);
+                           // dead before the P(k) pass writes `partials`, whose memory it shares
   float2* cbuf;            // batch x N x N x (N/2+1) combined C(m) (interlace codes 2, 3)
   double* coef;            // batch * kMaxBins adjoint coefficients
   uint64_t* mode_partials_n;  // kMaxBinBlocks * kMaxBins

@@ -51,10 +51,10 @@ __global__ __launch_bounds__(256) void k_set_counts(const int64_t* offsets, int6
 // Per set, weight_slices(batch) workgroups each sum w and w^2 over a fixed
 // slice of the set's particles (strided per thread, then a fixed tree over
 // the workgroup), and a second pass adds the slices in a fixed order: the totals
-// depend on the batch size only, not on scheduling.  Each slice also keeps its
-// largest mass and whether a mass is negative, NaN or infinite; the second
-// pass takes them to stats[4] (non-negative floats order like their bit
-// patterns) and stats[5].  One device-scope atomic per set: one per wave of
+// depend on the batch size only, not on scheduling.  Each slice also keeps the
+// bits of its largest mass (non-negative floats order like them), or ~0, above
+// any of them, if a mass is negative, NaN or infinite; the second pass takes
+// them to stats[4] and stats[5].  One device-scope atomic per set: one per wave of
 // every slice, all on one address, took 40 of the 52 us for 2M masses.
 constexpr int kWThreads = 256;
 
@@ -107,10 +107,10 @@ __global__ __launch_bounds__(kWThreads) void k_weight_stats(const float* __restr
       tm = max(tm, sm[i]);
       tbad |= sbad[i];
     }
-    double* dst = wpart + kWPartDoubles * ((int64_t)m * ns + slice);
-    dst[0] = ta;
-    dst[1] = tb;
-    reinterpret_cast<uint2*>(dst)[2] = make_uint2(tm, tbad);
+    const int64_t at = (int64_t)m * ns + slice;
+    wpart[2 * at] = ta;
+    wpart[2 * at + 1] = tb;
+    reinterpret_cast<uint32_t*>(wpart + 2 * (int64_t)gridDim.y * ns)[at] = tbad ? ~0u : tm;
   }
 }
 
@@ -122,12 +122,12 @@ __global__ __launch_bounds__(64) void k_weight_final(const double* __restrict__ 
   double ta = 0.0, tb = 0.0;
   uint32_t tm = 0u, bad = 0u;
   for (int i = lane; i < ns; i += 64) {
-    const double* src = wpart + kWPartDoubles * ((int64_t)m * ns + i);
-    ta += src[0];
-    tb += src[1];
-    const uint2 f = reinterpret_cast<const uint2*>(src)[2];
-    tm = max(tm, f.x);
-    bad |= f.y;
+    const int64_t at = (int64_t)m * ns + i;
+    ta += wpart[2 * at];
+    tb += wpart[2 * at + 1];
+    const uint32_t top = reinterpret_cast<const uint32_t*>(wpart + 2 * (int64_t)gridDim.x * ns)[at];
+    if (top == ~0u) bad = 1u;
+    else tm = max(tm, top);
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -685,8 +685,7 @@ __global__ __launch_bounds__(kColThreads) void k_sup_colscan(uint32_t* __restric
 template <typename TP>
 static hipError_t sort_two_level(const Geom& g, const TP* pos, const int64_t* offsets,
                                  int64_t n_total, const float* w, const Buffers& b, hipStream_t s) {
-  int nblk = (int)((n_total + 4095) / 4096);
-  if (nblk > kMaxSortBlocks) nblk = kMaxSortBlocks;
+  const int nblk = sort_blocks(n_total);
   const int64_t chunk = (n_total + nblk - 1) / nblk;
   hipLaunchKernelGGL(k_sort_hist<TP>, dim3(nblk), dim3(kSortThreads), 0, s, pos, n_total,
                      offsets, g, chunk, b.hsup, b.np, b.norm, b.stats);
@@ -694,10 +693,10 @@ static hipError_t sort_two_level(const Geom& g, const TP* pos, const int64_t* of
   if (e != hipSuccess) return e;
   if (w && (e = launch_weight_stats(w, offsets, n_total, g.batch, b.wpart, b.norm, b.stats, s)) != hipSuccess)
     return e;
-  // after the kMaxSortBlocks rows of histograms: the super-bucket starts
+  // after the nblk rows of histograms: the super-bucket starts
   // (base[nsup] = n_total) and totals.  Many workgroups: a column scan turns
   // the rows into per-block offsets and totals; few: the super pass does it.
-  uint32_t* base = b.hsup + (size_t)g.nsup * kMaxSortBlocks;
+  uint32_t* base = b.hsup + (size_t)g.nsup * nblk;
   uint32_t* tot = base + g.nsup + 1;
   const bool few = nblk <= kFewSortBlocks;
   if (!few)
