@@ -69,7 +69,7 @@ constexpr uint32_t kItemFrac = (1u << 25) - 1u;
 // IL: 0 one grid; 1 the interlaced pair; 2 a pair with run-time masks.
 // POW2: N is a power of two (cells wrap with a mask).  WT: masses.
 //
-// Per tile: (1) candidates, one per thread and round, become work items in
+// Per tile: (1) candidates, NC per thread and round, become work items in
 // registers, ranked inside their bank class by a returning LDS atomic;
 // (2) every wave scans the class counts for itself, and the items go to LDS
 // in class order such that the 32 lanes of a half wave take items spread
@@ -90,9 +90,16 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(WI
     int mask_a, int mask_b, int seg_len) {
   using AT = typename std::conditional<WIDE, unsigned long long, unsigned>::type;
   constexpr int NG = IL ? 2 : 1;
+  // candidates per thread and round: a grid alone takes two, for as many items
+  // as a pair has.  The half waves of a round then reach over more of the
+  // tile's buckets, and a clump narrower than a cell meets itself on fewer
+  // lanes: PCS on one grid, 16 clumped sets of 128^3, 0.88 -> 0.67 ms (32-bit,
+  // a particle in two cells) and 2.08 -> 1.57 (64-bit, one per cell); uniform
+  // particles 512^3, one per cell, 2.67 -> 2.46 ms.
+  constexpr int NC = IL ? 1 : 2;
   // candidates per round: fewer where 64-bit pairs with masses would leave
   // room for one workgroup per CU only
-  constexpr int kCand = (WIDE && WT && NG == 2) ? 384 : kWalkThreads;
+  constexpr int kCand = (WIDE && WT && NG == 2) ? 384 : NC * kWalkThreads;
   constexpr int kItems = NG * kCand;
   constexpr int kItemWords = WT ? 4 : 3;
   // y rows outside the tile add zeros in the 32-bit format (no test per row:
@@ -263,20 +270,27 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(WI
   Tile t = first_tile(b);
   int cur = 0;  // which of rgs holds this tile's runs
   int par = 0;  // which class counters the next round uses
-  // candidate c0 + lane of a tile with runs rg, its record loaded
-  uint4 cr = make_uint4(0u, 0u, 0u, 0u);
-  float cmass = 0.0f;
+  // candidates rb + e kWalkThreads + threadIdx.x (e < NC) of a tile with runs rg, their records loaded
+  uint4 cr[NC];
+  float cmass[NC];
+#pragma unroll
+  for (int e = 0; e < NC; ++e) {
+    cr[e] = make_uint4(0u, 0u, 0u, 0u);
+    cmass[e] = 0.0f;
+  }
   auto fetch = [&](const DepRanges& rg, uint32_t rb) __attribute__((always_inline)) {
     const int nr = rg.count;
     const uint32_t total = rg.pref[nr];
-    const uint32_t c0 = rb + (uint32_t)(wave * 64), cand = c0 + lane;
-    if (c0 < total && wave < kCand / 64) {
-      const int seg = find_segment(rg, nr, c0, cand, lane);
-      if (cand < total) {
-        const uint32_t j = rg.start[seg] + (cand - rg.pref[seg]);
-        cr = recs[j];
-        if constexpr (WT) cmass = sw[j];
+#pragma unroll
+    for (int e = 0; e < NC; ++e) {
+      const uint32_t c0 = rb + (uint32_t)(e * kWalkThreads + wave * 64), cand = c0 + lane;
+      uint32_t j = 0;
+      if (c0 < total && wave < kCand / NC / 64) {
+        const int seg = find_segment(rg, nr, c0, cand, lane);
+        if (cand < total) j = rg.start[seg] + (cand - rg.pref[seg]);
       }
+      cr[e] = recs[j];
+      if constexpr (WT) cmass[e] = sw[j];
     }
   };
   fetch(rgs[0], 0);
@@ -298,19 +312,22 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(WI
     }
 
     for (uint32_t rb = 0; rb < total; rb += kCand) {
-      // (1) this thread's candidate
-      const uint32_t cand = rb + threadIdx.x;
-      uint32_t w[NG][3];
-      bool ok[NG];
-      int cls[NG], rank[NG];
-      const float mass = cmass;
+      // (1) this thread's candidates
+      constexpr int NI = NG * NC;  // their items: e NG + grid
+      uint32_t w[NI][3];
+      bool ok[NI];
+      int cls[NI], rank[NI];
+      float mass[NC];
 #pragma unroll
-      for (int gi = 0; gi < NG; ++gi) {
-        ok[gi] = false;
-        cls[gi] = rank[gi] = 0;
+      for (int i = 0; i < NI; ++i) {
+        ok[i] = false;
+        cls[i] = rank[i] = 0;
       }
-      if (cand < total && wave < kCand / 64) {
-        const uint4 r = cr;
+#pragma unroll
+      for (int e = 0; e < NC; ++e) {
+        mass[e] = cmass[e];
+        if (rb + (uint32_t)(e * kWalkThreads) + threadIdx.x >= total || wave >= kCand / NC / 64) continue;
+        const uint4 r = cr[e];
         // first cells of the first grid, relative to the tile, plus p - 1
         const int ux = (int)(r.x & 1023u) - off - t0x + (P - 1);
         const int uy = (int)((r.x >> 10) & 1023u) - off - t0y + (P - 1);
@@ -328,24 +345,25 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(WI
         const bool own = !t.first || wrap(uz - (P - 1)) < ez;
 #pragma unroll
         for (int gi = 0; gi < NG; ++gi) {
+          const int i = e * NG + gi;
           const int mk = (IL == 2) ? (gi ? mask_b : mask_a) : (gi ? 7 : 0);
           const int stx = (int)((r.x >> 30) & 1u), sty = (int)(r.x >> 31), stz = (int)((r.y >> 24) & 1u);
           const bool hx = (mk & 1) != 0, hy = (mk & 2) != 0, hz = (mk & 4) != 0;
           const int qx = wrap(ux + (hx ? stx : 0)), qy = wrap(uy + (hy ? sty : 0));
           const int qz = wrap(uz + (hz ? stz : 0));
-          ok[gi] = qx < ex + P - 1 && qy < ey + P - 1 && (own || qz <= P - 1);
+          ok[i] = qx < ex + P - 1 && qy < ey + P - 1 && (own || qz <= P - 1);
           // the offset on this grid, as record_offset (particles.hpp)
           auto frac = [](uint32_t word, int step, bool shifted) {
             int v = (int)(word & kFracMask);
             if (shifted) v += step ? -(1 << (kFracBits - 1)) : (1 << (kFracBits - 1));
             return (uint32_t)v;
           };
-          w[gi][0] = frac(r.y, stx, hx) | ((uint32_t)qx << 25) | ((uint32_t)gi << 31);
-          w[gi][1] = frac(r.z, sty, hy) | ((uint32_t)qy << 25);
-          w[gi][2] = frac(r.w, stz, hz) | ((uint32_t)qz << 25);
-          cls[gi] = (qx * (kPlane & 63) + qy * kRow + qz) & 63;
-          if constexpr (WIDE) cls[gi] = ((cls[gi] << 1) & 63) | (cls[gi] >> 5);
-          if (ok[gi]) rank[gi] = atomicAdd(&cls_cnt[par][cls[gi]], 1);
+          w[i][0] = frac(r.y, stx, hx) | ((uint32_t)qx << 25) | ((uint32_t)gi << 31);
+          w[i][1] = frac(r.z, sty, hy) | ((uint32_t)qy << 25);
+          w[i][2] = frac(r.w, stz, hz) | ((uint32_t)qz << 25);
+          cls[i] = (qx * (kPlane & 63) + qy * kRow + qz) & 63;
+          if constexpr (WIDE) cls[i] = ((cls[i] << 1) & 63) | (cls[i] >> 5);
+          if (ok[i]) rank[i] = atomicAdd(&cls_cnt[par][cls[i]], 1);
         }
       }
       __syncthreads();
@@ -365,22 +383,28 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(WI
       par ^= 1;
       if (wave == 0) cls_cnt[par][lane] = 0;  // next used after this round's last barrier
 #pragma unroll
-      for (int gi = 0; gi < NG; ++gi) {
-        const int st = __shfl(start, cls[gi], 64);
-        if (ok[gi]) {
-          const uint32_t p = (uint32_t)(st + rank[gi]);
+      for (int i = 0; i < NI; ++i) {
+        const int st = __shfl(start, cls[i], 64);
+        if (ok[i]) {
+          const uint32_t p = (uint32_t)(st + rank[i]);
           const uint32_t l = __umulhi(p, hm);
           const uint32_t slot = (p - l * (uint32_t)H) * 32u + l;
-          items[slot] = w[gi][0];
-          items[kItems + slot] = w[gi][1];
-          items[2 * kItems + slot] = w[gi][2];
-          if constexpr (WT) items[3 * kItems + slot] = __float_as_uint(mass);
+          items[slot] = w[i][0];
+          items[kItems + slot] = w[i][1];
+          items[2 * kItems + slot] = w[i][2];
+          if constexpr (WT) items[3 * kItems + slot] = __float_as_uint(mass[i / NG]);
         }
       }
       __syncthreads();
-      // the next round's (or tile's) records are loaded during the stencils
-      if (rb + kCand < total) fetch(rgs[cur], rb + kCand);
-      else fetch(rgs[cur ^ 1], 0);
+      // the next round's (or tile's) records are loaded during the stencils, from
+      // one place in the code and, without a candidate, from record 0: with two
+      // places or a load in a branch the compiler copies the registers at the
+      // join, and waits for the loads there (512^3, one particle in eight
+      // cells, one grid: 0.57 -> 0.51 ms)
+      {
+        const bool more = rb + kCand < total;
+        fetch(rgs[more ? cur : cur ^ 1], more ? rb + kCand : 0u);
+      }
       // (3) the stencils
       for (int v = wave; v < W; v += kWalkWaves) {
         if (2 * v + (lane >> 5) + (lane & 31) * H >= m) continue;
