@@ -158,6 +158,65 @@ est_status check_config(const est_config* c) {
   return ok();
 }
 
+// Whether the deposit of n particles walks columns of 16 x 16 x 8 tiles: for
+// orders 1..4 on grids larger than a tile (PCS pair, 1024^3 with 2^27
+// particles: 5.73 against 6.41 ms).  Orders 1 and 2 on sparse grids stay with
+// the general kernel, whose 16^3 tiles halve the work per tile that is all
+// there is: with one particle in eight cells NGP pair 1024^3 3.89 against 4.91
+// ms and 512^3 0.53 against 0.62, CIC pair 4.25 against 4.87 (one CIC grid 3.33
+// and 3.43, 0.45 and 0.42 at 512^3); with one per cell the walk is faster
+// (256^3: NGP pair 0.21 against 0.25 ms, CIC 0.24 against 0.31).  Their 64-bit
+// format walks too (clustered NGP pair 512^3 0.75 against 0.97 ms).
+bool walks(const est_config& c, int64_t n) {
+  return c.order <= 4 && c.n_grid > kTileMax &&
+         (c.order > (c.interlace ? 2 : 1) || c.n_grid < 256 ||
+          4 * n >= (int64_t)c.batch * c.n_grid * c.n_grid * c.n_grid);
+}
+
+// Super-bucket edge fb for n particles: a divisor of nb from `least` up to
+// kFineMax, so that super-buckets tile the axis and a deposit run in z meets at
+// most one super-bucket edge: least 2 for the runs of up to 3 buckets of the
+// z-walking deposit, 5 (or nb itself) for the 6 of the general one (nb has no
+// prime factor above 5, so such a divisor exists when nb > kFineMax).  Of
+// these, the smallest whose super-bucket count batch (nb/fb)^3 stays at or
+// below n / 4096, so that the bucket pass scatters inside 64 KB and many
+// uneven super-buckets spread over the chip (512^3 clustered CIC: sort 0.83 ms
+// with 16K particles per super-bucket, 0.79 with 4K; 256^3 in lattice order
+// 0.343 and 0.331, in random order 0.702 and 0.730), but at small sizes below
+// n / 512, up to 512 super-buckets, so that the bucket pass has workgroups
+// (32768 particles on 64^3: sort 61 us with two super-buckets, 25 with 64).  If
+// none qualifies, the largest.  The count never falls as n grows.
+int super_edge(const est_config& c, int64_t n, int least) {
+  const int nb = c.n_grid / kBucket;
+  int64_t target = n / 512 < 512 ? n / 512 : 512;
+  if (target < n / 4096) target = n / 4096;
+  if (target < 1) target = 1;
+  if (target > kMaxSuper) target = kMaxSuper;
+  int largest = 0;
+  for (int d = 1; d <= kFineMax && d <= nb; ++d) {
+    if (nb % d != 0 || (d < least && d != nb)) continue;
+    largest = d;
+    const int64_t sa = nb / d;
+    if (c.batch * sa * sa * sa <= target) return d;
+  }
+  return largest;
+}
+
+// What depends on the particles of a call, not on the room of its handle: the
+// deposit kernel and the super-buckets of the sort (32768 particles on 128^3 in
+// a handle with room for 2^25: sort 83 us with that room's 4096 super-buckets,
+// 25 with their own 64).  No call has more super-buckets than the one that
+// fills the room, for which the workspace is laid out.
+void set_call(const est_config& c, int64_t n, Geom* g) {
+  g->walk = walks(c, n);
+  g->fb = super_edge(c, n, g->walk ? 2 : 5);
+  g->sa = g->nb / g->fb;
+  g->fb_mul = g->fb >= 2 ? (uint32_t)(4294967296ull / (uint64_t)g->fb + 1) : 0u;
+  const int64_t nsup = (int64_t)c.batch * g->sa * g->sa * g->sa;
+  // the two-level sort runs when nsup <= kMaxSuper; a larger value selects the atomic sort
+  g->nsup = ((c.flags & EST_FLAG_ATOMIC_SORT) || nsup > kMaxSuper) ? kMaxSuper + 1 : (int)nsup;
+}
+
 Geom make_geom(const est_config& c) {
   Geom g;
   g.n = c.n_grid;
@@ -169,51 +228,7 @@ Geom make_geom(const est_config& c) {
   g.il = c.interlace ? 1 : 0;
   g.batch = c.batch;
   g.nb = c.n_grid / kBucket;
-  // The deposit walks columns of 16 x 16 x 8 tiles for orders 1..4 on grids
-  // larger than a tile (PCS pair, 1024^3 with 2^27 particles: 5.73 against 6.41
-  // ms).  Orders 1 and 2 on sparse grids stay with the general kernel, whose
-  // 16^3 tiles halve the work per tile that is all there is: with one particle
-  // in eight cells NGP pair 1024^3 3.89 against 4.91 ms and 512^3 0.53 against
-  // 0.62, CIC pair 4.25 against 4.87 (one CIC grid 3.33 and 3.43, 0.45 and
-  // 0.42 at 512^3); with one per cell the walk is faster
-  // (256^3: NGP pair 0.21 against 0.25 ms, CIC 0.24 against 0.31).  Their
-  // 64-bit format walks too (clustered NGP pair 512^3 0.75 against 0.97 ms).
-  g.walk = c.order <= 4 && c.n_grid > kTileMax &&
-           (c.order > (c.interlace ? 2 : 1) || c.n_grid < 256 ||
-            4 * c.max_particles >= (int64_t)c.batch * c.n_grid * c.n_grid * c.n_grid);
-  // Super-bucket edge fb: a divisor of nb up to kFineMax, so super-buckets
-  // tile the axis, and long enough that a deposit run in z meets at most one
-  // super-bucket edge: 2 for the runs of up to 3 buckets of the z-walking
-  // deposit, 5 (or nb itself) for the 6 of the general one (nb has no prime
-  // factor above 5, so such a divisor exists when nb > kFineMax).
-  // Of these, the smallest whose super-bucket count batch (nb/fb)^3 stays at
-  // or below max_particles / 4096, so that the bucket pass scatters inside
-  // 64 KB and many uneven super-buckets spread over the chip (512^3 clustered
-  // CIC: sort 0.83 ms with 16K particles per super-bucket, 0.79 with 4K; 256^3
-  // in lattice order 0.343 and 0.331, in random order 0.702 and 0.730), but at
-  // small sizes below max_particles / 512, up to 512 super-buckets, so that
-  // the bucket pass has workgroups (32768 particles on 64^3: sort 61 us with
-  // two super-buckets, 25 with 64).  If none qualifies, the largest.
-  {
-    const int least = g.walk ? 2 : 5;
-    int64_t target = c.max_particles / 512 < 512 ? c.max_particles / 512 : 512;
-    if (target < c.max_particles / 4096) target = c.max_particles / 4096;
-    if (target < 1) target = 1;
-    if (target > kMaxSuper) target = kMaxSuper;
-    int small_ok = 0, largest = 0;
-    for (int d = 1; d <= kFineMax && d <= g.nb; ++d) {
-      if (g.nb % d != 0 || (d < least && d != g.nb)) continue;
-      largest = d;
-      const int64_t sa = g.nb / d;
-      if (!small_ok && (int64_t)c.batch * sa * sa * sa <= target) small_ok = d;
-    }
-    g.fb = small_ok ? small_ok : largest;
-  }
-  g.sa = g.nb / g.fb;
-  g.fb_mul = g.fb >= 2 ? (uint32_t)(4294967296ull / (uint64_t)g.fb + 1) : 0u;
-  const int64_t nsup = (int64_t)c.batch * g.sa * g.sa * g.sa;
-  // the two-level sort runs when nsup <= kMaxSuper; a larger value selects the atomic sort
-  g.nsup = ((c.flags & EST_FLAG_ATOMIC_SORT) || nsup > kMaxSuper) ? kMaxSuper + 1 : (int)nsup;
+  set_call(c, c.max_particles, &g);
   g.tile = c.n_grid < kTileMax ? c.n_grid : kTileMax;
   g.box = c.box;
   g.inv = (double)c.n_grid / c.box;
@@ -322,14 +337,16 @@ est_status ensure_modes(est_handle h, int n_dk, int n_bins) {
 est_status run_deposit(est_handle h, const void* pos, est_dtype dt, const int64_t* offsets,
                        int64_t n_total) {
   est_status st;
+  Geom g = h->g;
+  set_call(h->cfg, n_total, &g);
   {
     ProfScope ps(h, kPSort);
-    st = dev_err(launch_sort(h->g, pos, dt, offsets, n_total, h->weights, h->b, h->stream),
+    st = dev_err(launch_sort(g, pos, dt, offsets, n_total, h->weights, h->b, h->stream),
                  "bucket sort");
     if (st) return st;
   }
   ProfScope ps(h, kPDeposit);
-  return dev_err(launch_deposit(h->g, h->b, h->tu, h->weights != nullptr, h->stream), "deposit");
+  return dev_err(launch_deposit(g, h->b, h->tu, h->weights != nullptr, h->stream), "deposit");
 }
 
 est_status run_xy(est_handle h, int dir) {
