@@ -160,17 +160,42 @@ est_status check_config(const est_config* c) {
 
 // Whether the deposit of n particles walks columns of 16 x 16 x 8 tiles: for
 // orders 1..4 on grids larger than a tile (PCS pair, 1024^3 with 2^27
-// particles: 5.73 against 6.41 ms).  Orders 1 and 2 on sparse grids stay with
-// the general kernel, whose 16^3 tiles halve the work per tile that is all
-// there is: with one particle in eight cells NGP pair 1024^3 3.89 against 4.91
-// ms and 512^3 0.53 against 0.62, CIC pair 4.25 against 4.87 (one CIC grid 3.33
-// and 3.43, 0.45 and 0.42 at 512^3); with one per cell the walk is faster
-// (256^3: NGP pair 0.21 against 0.25 ms, CIC 0.24 against 0.31).  Their 64-bit
-// format walks too (clustered NGP pair 512^3 0.75 against 0.97 ms).
+// particles: 5.73 against 6.41 ms), unless the grids are large and sparse:
+// there the work per tile is all there is, and the 16^3 tiles of the general
+// kernel halve it.  (Only the 32-bit format; the 64-bit one of clustered
+// particles always walks: NGP pair 512^3 0.75 against 0.97 ms.)  The line is
+// where the two meet, by cells per particle; walk / general of the deposit on
+// both sides of it (general before the stroke):
+//   one grid   order 1  1/4: 1.07 .. 1.14 | 1/2: 0.92      2, 3  1/12: 0.99 .. 1.33 | 1/8: 0.92 .. 1.03
+//              order 4  1/16: 1.07 .. 1.35 | 1/8: 0.90 .. 0.98 (masses 1/64: 1.11 | 1/16: 0.95)
+//   the pair   order 1  1/4: 1.02 .. 1.06 | 1/2: 0.88      2  1/8: 1.02 .. 1.13 | 1/4: 0.91
+//              order 3  1/16: 1.04 .. 1.14 | 1/12: 0.96    4  1/32: 1.05 .. 1.13 | 1/16: 0.96
+//   4, 8 grids order 1  1/8: 1.02 .. 1.15 | 1/4: 0.95 .. 1.00  2  1/12: 1.03 .. 1.10 | 1/8: 0.91 .. 1.06
+//              order 3  1/16: 1.03 .. 1.12 | 1/8: 0.88     4  1/32: 1.08 .. 1.21 | 1/16: 0.96
+// (320^3 to 1024^3 and batches of as many cells; one grid from 256^3).  Smaller
+// grids leave the general kernel too few tiles: below about 290^3 cells in all
+// it pays with several grids only where next to nothing is left per tile
+// (256^3 pair, 1/64: order 3 and masses 1.12, else 0.97 .. 1.00; four grids of
+// 160^3 to 216^3, 1/64: 1.05 .. 1.23), below 160^3 never.
 bool walks(const est_config& c, int64_t n) {
-  return c.order <= 4 && c.n_grid > kTileMax &&
-         (c.order > (c.interlace ? 2 : 1) || c.n_grid < 256 ||
-          4 * n >= (int64_t)c.batch * c.n_grid * c.n_grid * c.n_grid);
+  if (c.order > 4 || c.n_grid <= kTileMax) return false;
+  const int64_t cells = (int64_t)c.batch * c.n_grid * c.n_grid * c.n_grid;
+  const bool masses = (c.flags & EST_FLAG_WEIGHTS) != 0;
+  static const int one[4] = {4, 12, 12, 16}, pair[4] = {4, 8, 16, 32}, more[4] = {8, 12, 16, 32};
+  int per;  // least cells per particle of the general kernel
+  if (cells < 4000000) return true;  // 160^3
+  if (c.interlace == 0) {
+    per = cells < (1 << 24) ? 16 : one[c.order - 1];
+    if (masses && c.order == 4) per = 32;
+  } else if (cells >= 3 << 23) {  // 293^3
+    per = c.interlace == 1 ? pair[c.order - 1] : more[c.order - 1];
+  } else if (c.interlace > 1) {
+    per = cells < (1 << 24) ? 64 : 32;
+  } else {
+    if (cells < (1 << 24) || !(masses || c.order == 3)) return true;
+    per = 64;
+  }
+  return n * per > cells;
 }
 
 // Super-bucket edge fb for n particles: a divisor of nb from `least` up to

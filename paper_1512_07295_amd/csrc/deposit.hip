@@ -197,11 +197,12 @@ __device__ __forceinline__ void deposit_item(uint4 rec, int gi, const Geom& g, i
 // a separate instantiation so that the equal-mass kernel keeps its registers
 // IL: 0 one grid; 1 the interlaced pair (masks 0 and 7); 2 a pair of grids
 // with run-time masks (mask_a, mask_b) written to slab q of each set
-// 32-bit pairs of orders 1 and 2 on grids larger than a tile: capped at 64
-// VGPRs (no scratch), so that two workgroups of 1024 threads fit in a CU
+// 32-bit pairs of orders 1, 2 and 4 on grids larger than a tile: capped at 64
+// VGPRs (no scratch; order 3 would spill), so that two workgroups of 1024
+// threads fit in a CU
 template <int P, int IL, bool WIDE, int WRAP, bool WT>
 __host__ __device__ constexpr bool two_groups_per_cu() {
-  return P <= 2 && IL == 1 && !WIDE && !WT && WRAP != kPeriodic;
+  return (P <= 2 || P == 4) && IL == 1 && !WIDE && !WT && WRAP != kPeriodic;
 }
 
 template <int P, int IL, bool WIDE, int WRAP, bool WT>
@@ -645,16 +646,18 @@ static hipError_t deposit_launch(const Geom& g, const Buffers& b, int threads, b
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  if constexpr (P <= 4 && WRAP != kPeriodic) return hipSuccess;  // the walk's 64-bit kernel follows
-  // the 64-bit kernel holds one workgroup per CU; it takes units from a
-  // counter, so when the 32-bit kernel does the work it costs one short wave
-  // per workgroup
-  const unsigned wblocks = (unsigned)(nunits < 1024 ? nunits : 1024);
-  hipLaunchKernelGGL((k_deposit<P, IL, true, WRAP, WT>), dim3(wblocks),
-                     dim3(threads ? threads : 512), 0, s, (const uint4*)b.recs, b.boff, b.bcnt,
-                     (float*)b.grid, g, b.stats, narrow ? 0 : 1, 1, 0, sw, q, ma, mb,
-                     walk ? 1 : 0, seg);
-  return hipGetLastError();
+  // the 64-bit kernel (of orders 1..4 on grids larger than a tile: the walk's)
+  // holds one workgroup per CU; it takes units from a counter, so when the
+  // 32-bit kernel does the work it costs one short wave per workgroup
+  if constexpr (P >= 5 || WRAP == kPeriodic) {
+    const unsigned wblocks = (unsigned)(nunits < 1024 ? nunits : 1024);
+    hipLaunchKernelGGL((k_deposit<P, IL, true, WRAP, WT>), dim3(wblocks),
+                       dim3(threads ? threads : 512), 0, s, (const uint4*)b.recs, b.boff, b.bcnt,
+                       (float*)b.grid, g, b.stats, narrow ? 0 : 1, 1, 0, sw, q, ma, mb,
+                       walk ? 1 : 0, seg);
+    return hipGetLastError();
+  }
+  return hipSuccess;
 }
 
 template <int P, int IL, int WRAP>
@@ -671,15 +674,13 @@ static hipError_t dispatch_deposit_t(const Geom& g, const Buffers& b, const Tune
   const bool xcd = tu.dep_xcd != 0;
   if (g.tile == g.n)
     return dispatch_deposit_w<P, IL, kPeriodic>(g, b, threads, narrow, xcd, tu.cus, sw, q, ma, mb, s);
-  // 32-bit format of orders 1 and 2 on sparse grids, both of orders 5 and 6
-  if constexpr (P <= 2 || P >= 5) {
-    if (P >= 5 || (!g.walk && narrow)) {
-      const hipError_t e =
-          (g.n & (g.n - 1)) == 0
-              ? dispatch_deposit_w<P, IL, kMasked>(g, b, threads, narrow, xcd, tu.cus, sw, q, ma, mb, s)
-              : dispatch_deposit_w<P, IL, kGeneral>(g, b, threads, narrow, xcd, tu.cus, sw, q, ma, mb, s);
-      if (P >= 5 || e != hipSuccess) return e;
-    }
+  // the 32-bit format of orders 1..4 on sparse grids, both formats of orders 5 and 6
+  if (P >= 5 || (!g.walk && narrow)) {
+    const hipError_t e =
+        (g.n & (g.n - 1)) == 0
+            ? dispatch_deposit_w<P, IL, kMasked>(g, b, threads, narrow, xcd, tu.cus, sw, q, ma, mb, s)
+            : dispatch_deposit_w<P, IL, kGeneral>(g, b, threads, narrow, xcd, tu.cus, sw, q, ma, mb, s);
+    if (P >= 5 || e != hipSuccess) return e;
   }
   return launch_deposit_walk(g, b, tu, sw, q, ma, mb, s);
 }

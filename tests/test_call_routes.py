@@ -56,3 +56,44 @@ for n_grid, batch in ((20, 1), (64, 3), (100, 1), (256, 1), (300, 2), (320, 1), 
                     assert now[0] >= last[0] and now[1] >= last[1], (n_grid, batch, order, code, weights, n)
                     last = now
 ''')
+
+
+def test_sparse_grids_take_the_general_deposit():
+    """(n_grid, batch, order, interlace, masses, cells per particle, general):
+    both sides of each line, and both kinds of kernel in the 64-bit format."""
+    stub_common.run(SHAPES + '''
+lines = []
+for n_grid, batch in ((512, 1), (300, 1), (128, 16), (64, 128)):
+    for code, per in ((0, (4, 12, 12, 16)), (1, (4, 8, 16, 32)), (2, (8, 12, 16, 32)), (3, (8, 12, 16, 32))):
+        for order in (1, 2, 3, 4):
+            lines.append((n_grid, batch, order, code, False, per[order - 1]))
+    lines += [(n_grid, batch, 4, 0, True, 32), (n_grid, batch, 3, 0, True, 12), (n_grid, batch, 4, 1, True, 32)]
+for order in (1, 2, 3, 4):
+    lines += [(256, 1, order, 1, order != 3, 64), (256, 1, order, 3, False, 32), (160, 1, order, 0, False, 16),
+              (200, 1, order, 2, False, 64), (96, 5, order, 0, False, 16)]
+    lines += [(128, 1, order, code, False, None) for code in range(4)] + [(240, 1, order, 1, False, None)]
+    lines += [(256, 1, order, 1, False, None)] if order != 3 else []
+for n_grid, batch, order, code, masses, per in lines:
+    cells = batch * n_grid ** 3
+    for n, general in ((cells // per, True), (cells // per + 1, False)) if per else ((cells // 1000, False), (cells, False)):
+        names = [name for name, _, _ in shapes(n_grid, order, code, batch, n, n, masses) if "k_deposit" in name]
+        first = "k_depositILi%dELi%dELb0" % (order, min(code, 2)) if general else "k_deposit_walkILi%dELi%dELb0" % (order, min(code, 2))
+        assert all(first in a and "k_deposit_walkILi%d" % order in b and "ELb1ELb" in b for a, b in zip(names[::2], names[1::2])), \\
+            (n_grid, batch, order, code, masses, n, names)
+''')
+
+
+def test_every_deposit_kernel_is_reached():
+    """No kernel of the deposit is compiled that no call can launch."""
+    out = stub_common.run(SHAPES + '''
+stub.stub_kernel.restype = ctypes.c_char_p
+seen = set()
+for n_grid, batch, n in ((16, 1, 100), (64, 1, 100), (40, 1, 100), (512, 1, 100), (500, 1, 100)):
+    for order in range(1, 7):
+        for code in (0, 1, 2):
+            for weights in (False, True):
+                seen |= {name for name, _, _ in shapes(n_grid, order, code, batch, n, n, weights)}
+names = {stub.stub_kernel(i).decode() for i in range(stub.stub_kernels())}
+print(sorted(name for name in names - seen if "k_deposit" in name))
+''')
+    assert out.strip() == "[]"
