@@ -193,8 +193,14 @@ bool walks(const est_config& c, int64_t n) {
     per = cells < (1 << 24) ? 64 : 32;
   } else {
     if (cells < (1 << 24) || !(masses || c.order == 3)) return true;
-    per = 64;
+    per = masses ? 32 : 64;
   }
+  // next to empty grids of orders 3 and 4 walk again, several at a time (360^3,
+  // order 4, pair 1/8192: 0.78, 1/512: 0.97; four 1/8192: 0.97, 1/2048: 1.01), and
+  // so does a pair of order 4 on smaller grids, for clumped particles (1/32:
+  // 128^3 in batches 0.91, 300^3 0.97, 512^3 1.09)
+  if (c.interlace && c.order >= 3 && (c.interlace == 1 ? 1024 : 2048) * n < cells) return true;
+  if (c.interlace == 1 && c.order == 4 && !masses && c.n_grid < 400) return true;
   return n * per > cells;
 }
 
@@ -230,10 +236,10 @@ int super_edge(const est_config& c, int64_t n, int least) {
 // What depends on the particles of a call, not on the room of its handle: the
 // deposit kernel and the super-buckets of the sort (32768 particles on 128^3 in
 // a handle with room for 2^25: sort 83 us with that room's 4096 super-buckets,
-// 25 with their own 64).  No call has more super-buckets than the one that
-// fills the room, for which the workspace is laid out.
-void set_call(const est_config& c, int64_t n, Geom* g) {
-  g->walk = walks(c, n);
+// 25 with their own 64).  No call has more super-buckets than one that fills the
+// room and walks, for which the workspace is laid out.
+void set_call(const est_config& c, int64_t n, bool walk, Geom* g) {
+  g->walk = walk;
   g->fb = super_edge(c, n, g->walk ? 2 : 5);
   g->sa = g->nb / g->fb;
   g->fb_mul = g->fb >= 2 ? (uint32_t)(4294967296ull / (uint64_t)g->fb + 1) : 0u;
@@ -253,7 +259,7 @@ Geom make_geom(const est_config& c) {
   g.il = c.interlace ? 1 : 0;
   g.batch = c.batch;
   g.nb = c.n_grid / kBucket;
-  set_call(c, c.max_particles, &g);
+  set_call(c, c.max_particles, c.order <= 4 && c.n_grid > kTileMax, &g);
   g.tile = c.n_grid < kTileMax ? c.n_grid : kTileMax;
   g.box = c.box;
   g.inv = (double)c.n_grid / c.box;
@@ -363,7 +369,7 @@ est_status run_deposit(est_handle h, const void* pos, est_dtype dt, const int64_
                        int64_t n_total) {
   est_status st;
   Geom g = h->g;
-  set_call(h->cfg, n_total, &g);
+  set_call(h->cfg, n_total, walks(h->cfg, n_total), &g);
   {
     ProfScope ps(h, kPSort);
     st = dev_err(launch_sort(g, pos, dt, offsets, n_total, h->weights, h->b, h->stream),

@@ -63,19 +63,22 @@ def test_sparse_grids_take_the_general_deposit():
     both sides of each line, and both kinds of kernel in the 64-bit format."""
     stub_common.run(SHAPES + '''
 lines = []
-for n_grid, batch in ((512, 1), (300, 1), (128, 16), (64, 128)):
-    for code, per in ((0, (4, 12, 12, 16)), (1, (4, 8, 16, 32)), (2, (8, 12, 16, 32)), (3, (8, 12, 16, 32))):
+for n_grid, batch in ((512, 1), (400, 1), (128, 16), (64, 128)):
+    for code, per in ((0, (4, 12, 12, 16)), (1, (4, 8, 16, 32 if n_grid >= 400 else None)), (2, (8, 12, 16, 32)), (3, (8, 12, 16, 32))):
         for order in (1, 2, 3, 4):
             lines.append((n_grid, batch, order, code, False, per[order - 1]))
     lines += [(n_grid, batch, 4, 0, True, 32), (n_grid, batch, 3, 0, True, 12), (n_grid, batch, 4, 1, True, 32)]
 for order in (1, 2, 3, 4):
-    lines += [(256, 1, order, 1, order != 3, 64), (256, 1, order, 3, False, 32), (160, 1, order, 0, False, 16),
-              (200, 1, order, 2, False, 64), (96, 5, order, 0, False, 16)]
+    lines += [(256, 1, order, 1, True, 32), (256, 1, order, 1, False, 64 if order == 3 else None), (256, 1, order, 3, False, 32),
+              (160, 1, order, 0, False, 16), (200, 1, order, 2, False, 64), (96, 5, order, 0, False, 16)]
     lines += [(128, 1, order, code, False, None) for code in range(4)] + [(240, 1, order, 1, False, None)]
-    lines += [(256, 1, order, 1, False, None)] if order != 3 else []
 for n_grid, batch, order, code, masses, per in lines:
     cells = batch * n_grid ** 3
-    for n, general in ((cells // per, True), (cells // per + 1, False)) if per else ((cells // 1000, False), (cells, False)):
+    counts = [(cells // per, True), (cells // per + 1, False)] if per else [(cells // 1000, False), (cells // 64, False), (cells, False)]
+    if per and code and order >= 3:  # next to empty
+        edge = -(-cells // (1024 if code == 1 else 2048))
+        counts += [(edge, True), (edge - 1, False)]
+    for n, general in counts:
         names = [name for name, _, _ in shapes(n_grid, order, code, batch, n, n, masses) if "k_deposit" in name]
         first = "k_depositILi%dELi%dELb0" % (order, min(code, 2)) if general else "k_deposit_walkILi%dELi%dELb0" % (order, min(code, 2))
         assert all(first in a and "k_deposit_walkILi%d" % order in b and "ELb1ELb" in b for a, b in zip(names[::2], names[1::2])), \\
@@ -88,7 +91,7 @@ def test_every_deposit_kernel_is_reached():
     out = stub_common.run(SHAPES + '''
 stub.stub_kernel.restype = ctypes.c_char_p
 seen = set()
-for n_grid, batch, n in ((16, 1, 100), (64, 1, 100), (40, 1, 100), (512, 1, 100), (500, 1, 100)):
+for n_grid, batch, n in ((16, 1, 100), (64, 1, 100), (40, 1, 100), (512, 1, 10 ** 6), (500, 1, 10 ** 6)):
     for order in range(1, 7):
         for code in (0, 1, 2):
             for weights in (False, True):
