@@ -213,14 +213,19 @@ bool walks(const est_config& c, int64_t n) {
 // below n / 4096, so that the bucket pass scatters inside 64 KB and many
 // uneven super-buckets spread over the chip (512^3 clustered CIC: sort 0.83 ms
 // with 16K particles per super-bucket, 0.79 with 4K; 256^3 in lattice order
-// 0.343 and 0.331, in random order 0.702 and 0.730), but at small sizes below
-// n / 512, up to 512 super-buckets, so that the bucket pass has workgroups
-// (32768 particles on 64^3: sort 61 us with two super-buckets, 25 with 64).  If
-// none qualifies, the largest.  The count never falls as n grows.
-int super_edge(const est_config& c, int64_t n, int least) {
+// 0.343 and 0.331, in random order 0.702 and 0.730).  With masses n / 16384: a
+// mass is a second scattered write, of 4 bytes, in both passes (256^3, one
+// particle per cell: in random order 1.74 ms with 4K particles per super-bucket,
+// 1.28 with 16K, in lattice order 0.64 and 0.50; 512^3, one in eight cells,
+// 1.85 and 1.45).  At small sizes up to 512 super-buckets, so that the bucket
+// pass has workgroups: below n / 512 (32768 particles on 64^3: sort 61 us with
+// two super-buckets, 25 with 64).  If none qualifies, the largest.  The count
+// never falls as n grows.
+int super_edge(const est_config& c, int64_t n, bool masses, int least) {
   const int nb = c.n_grid / kBucket;
   int64_t target = n / 512 < 512 ? n / 512 : 512;
-  if (target < n / 4096) target = n / 4096;
+  const int64_t most = n / (masses ? 16384 : 4096);
+  if (target < most) target = most;
   if (target < 1) target = 1;
   if (target > kMaxSuper) target = kMaxSuper;
   int largest = 0;
@@ -237,10 +242,10 @@ int super_edge(const est_config& c, int64_t n, int least) {
 // deposit kernel and the super-buckets of the sort (32768 particles on 128^3 in
 // a handle with room for 2^25: sort 83 us with that room's 4096 super-buckets,
 // 25 with their own 64).  No call has more super-buckets than one that fills the
-// room and walks, for which the workspace is laid out.
-void set_call(const est_config& c, int64_t n, bool walk, Geom* g) {
+// room, walks and has no masses, for which the workspace is laid out.
+void set_call(const est_config& c, int64_t n, bool masses, bool walk, Geom* g) {
   g->walk = walk;
-  g->fb = super_edge(c, n, g->walk ? 2 : 5);
+  g->fb = super_edge(c, n, masses, g->walk ? 2 : 5);
   g->sa = g->nb / g->fb;
   g->fb_mul = g->fb >= 2 ? (uint32_t)(4294967296ull / (uint64_t)g->fb + 1) : 0u;
   const int64_t nsup = (int64_t)c.batch * g->sa * g->sa * g->sa;
@@ -259,7 +264,7 @@ Geom make_geom(const est_config& c) {
   g.il = c.interlace ? 1 : 0;
   g.batch = c.batch;
   g.nb = c.n_grid / kBucket;
-  set_call(c, c.max_particles, c.order <= 4 && c.n_grid > kTileMax, &g);
+  set_call(c, c.max_particles, false, c.order <= 4 && c.n_grid > kTileMax, &g);
   g.tile = c.n_grid < kTileMax ? c.n_grid : kTileMax;
   g.box = c.box;
   g.inv = (double)c.n_grid / c.box;
@@ -369,7 +374,7 @@ est_status run_deposit(est_handle h, const void* pos, est_dtype dt, const int64_
                        int64_t n_total) {
   est_status st;
   Geom g = h->g;
-  set_call(h->cfg, n_total, walks(h->cfg, n_total), &g);
+  set_call(h->cfg, n_total, h->weights != nullptr, walks(h->cfg, n_total), &g);
   {
     ProfScope ps(h, kPSort);
     st = dev_err(launch_sort(g, pos, dt, offsets, n_total, h->weights, h->b, h->stream),

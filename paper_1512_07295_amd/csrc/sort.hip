@@ -121,13 +121,17 @@ __global__ __launch_bounds__(64) void k_weight_final(const double* __restrict__ 
   const int m = blockIdx.x, lane = threadIdx.x;
   double ta = 0.0, tb = 0.0;
   uint32_t tm = 0u, bad = 0u;
+  const double2* sums = reinterpret_cast<const double2*>(wpart) + (int64_t)m * ns;
+  const uint32_t* tops = reinterpret_cast<const uint32_t*>(wpart + 2 * (int64_t)gridDim.x * ns) + (int64_t)m * ns;
+  // four slices' loads in flight together (at most 1024 slices)
+#pragma unroll 4
   for (int i = lane; i < ns; i += 64) {
-    const int64_t at = (int64_t)m * ns + i;
-    ta += wpart[2 * at];
-    tb += wpart[2 * at + 1];
-    const uint32_t top = reinterpret_cast<const uint32_t*>(wpart + 2 * (int64_t)gridDim.x * ns)[at];
-    if (top == ~0u) bad = 1u;
-    else tm = max(tm, top);
+    const double2 s = sums[i];
+    const uint32_t top = tops[i];
+    ta += s.x;
+    tb += s.y;
+    bad |= top == ~0u ? 1u : 0u;
+    tm = max(tm, top == ~0u ? 0u : top);
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
