@@ -219,11 +219,15 @@ bool walks(const est_config& c, int64_t n) {
 // 1.28 with 16K, in lattice order 0.64 and 0.50; 512^3, one in eight cells,
 // 1.85 and 1.45).  At small sizes up to 512 super-buckets, so that the bucket
 // pass has workgroups: below n / 512 (32768 particles on 64^3: sort 61 us with
-// two super-buckets, 25 with 64).  If none qualifies, the largest.  The count
-// never falls as n grows.
+// two super-buckets, 25 with 64), or one per 512 buckets, whose offsets the
+// bucket pass writes (4096 particles on 128^3: 25 us with 8 super-buckets, 23 with
+// 64).  If none qualifies, the largest.  The count never falls as n grows.
 int super_edge(const est_config& c, int64_t n, bool masses, int least) {
   const int nb = c.n_grid / kBucket;
+  const int64_t buckets = (int64_t)c.batch * nb * nb * nb;
   int64_t target = n / 512 < 512 ? n / 512 : 512;
+  const int64_t least_count = buckets / 512 < 64 ? buckets / 512 : 64;
+  if (target < least_count) target = least_count;
   const int64_t most = n / (masses ? 16384 : 4096);
   if (target < most) target = most;
   if (target < 1) target = 1;

@@ -111,3 +111,13 @@ for n_grid, n, plain, masses in ((256, 1 << 24, 4096, 512), (512, 1 << 24, 4096,
         scan = [g for name, g, _ in shapes(n_grid, 4, 1, 1, n, n, weights) if "k_sup_colscan" in name]
         assert scan == [-(-count // 64)], (n_grid, n, weights, scan)
 ''')
+
+
+def test_few_particles_keep_workgroups_in_the_bucket_pass():
+    """Its workgroups write the offsets of every bucket, at most 512 each here."""
+    stub_common.run(SHAPES + '''
+for n_grid, batch, least in ((64, 1, 8), (128, 1, 64), (256, 1, 64), (64, 8, 64), (512, 1, 512)):
+    for n in (1, 100, 4096):
+        fine = [g for name, g, _ in shapes(n_grid, 4, 1, batch, 1 << 22, n) if "k_sort_fine" in name]
+        assert fine[0] >= least, (n_grid, batch, n, fine)
+''')
