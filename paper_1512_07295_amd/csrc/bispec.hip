@@ -28,7 +28,10 @@
 //     and each wave keeps up to 16 jobs' accumulators in registers: FP32
 //     products and sums over a chunk, FP64 across chunks.  The jobs are split
 //     evenly over the waves: with the first waves full and the others idle,
-//     32 shells on 200^3 (35 jobs) took 0.46 ms per slab, now 0.19;
+//     32 shells on 200^3 (35 jobs) took 0.46 ms per slab, now 0.19.  Not so
+//     over the groups where that leaves a wave of 16 jobs in each anyway (996
+//     jobs of 128 shells): full groups and a lighter last one took 20.3 ms per
+//     slab of 400^3, eight equal ones 21.9;
 //  5. per-workgroup sums are reduced in a fixed order, slab after slab.
 // The J sums depend only on (M, n_dk, n_bins, the jobs) and are cached by the
 // caller (api.hip) after the first call.
@@ -46,9 +49,11 @@ constexpr int kBsMaxS = 32;          // x planes per slab, at most
 constexpr int kBsWaves = 8;          // waves of a triple-sum workgroup
 constexpr int kBsJobsPerWave = 16;   // 16x16 tiles whose accumulators a wave holds
 constexpr int kBsJobsPerGroup = kBsWaves * kBsJobsPerWave;
-// triple-sum workgroups per slab, about: two rounds over the CUs (one
+// triple-sum workgroups per slab, at most: two rounds over the CUs (one
 // workgroup each, by its registers); more only add partial sums to write and
-// reduce (32 shells on 200^3: 1024 ranges took 0.26 ms per slab to reduce)
+// reduce (32 shells on 200^3: 1024 ranges took 0.26 ms per slab to reduce), and
+// a few above it a third round (100 shells, 515 of them 13.7 ms per slab of
+// 320^3, 510 9.6; 150 shells on 480^3, 520 106 ms, 507 78)
 constexpr int kBsTargetBlocks = 512;
 constexpr size_t kBsSlabBudget = (size_t)8 << 30;  // bytes of one slab's fields, at most
 
@@ -91,7 +96,7 @@ bool bs_plan(int n, int n_dk, int n_bins, int64_t njobs, int64_t n_tri, BsPlan* 
   const int64_t chunks = (p.npts + p.pc - 1) / p.pc;
   p.njobs = njobs;
   p.ngroups = (int)((njobs + kBsJobsPerGroup - 1) / kBsJobsPerGroup);
-  int64_t nr = (kBsTargetBlocks + p.ngroups - 1) / (p.ngroups > 0 ? p.ngroups : 1);
+  int64_t nr = kBsTargetBlocks / (p.ngroups > 0 ? p.ngroups : 1);
   if (nr > chunks) nr = chunks;
   p.nranges = (int)(nr > 0 ? nr : 1);
   // workspace: twiddles, the delta cube, one slab, jobs, triangle map,
@@ -278,14 +283,15 @@ __global__ __launch_bounds__(256) void k_bs_xdft(const float2* __restrict__ band
 // (d, r0, c0) is the 16x16 tile T(i, j) = sum_p I_b1 I_b2 I_b3 with
 // b2 = bs + 16 r0 + i, b1 = b2 + d, b3 = bs + 16 c0 + j, bs = max(d, 1)
 // (shells above n_bins read a zero row).  Workgroup = (point range, job
-// group); the jobs are split evenly over the groups' waves.  MFMA
+// group of `per_group` jobs, or an equal share if that is 0); a group's jobs
+// are split evenly over its waves.  MFMA
 // v_mfma_f32_16x16x4f32: lane l supplies A[l % 16][l / 16] and
 // B[l / 16][l % 16] and holds D[4 (l / 16) + r][l % 16] in register r; lane
 // l's four K-slots of the PC/4 steps are the points (l / 16) PC/4 + s.
 template <int PC, int JPW>
 __global__ __launch_bounds__(kBsWaves * 64, JPW <= 8 ? 4 : 2) void k_bs_triple(
     const float2* __restrict__ slab, int64_t npts, int Q, int n_bins,
-    const int32_t* __restrict__ jobs, int njobs, int ngroups, int nranges,
+    const int32_t* __restrict__ jobs, int njobs, int ngroups, int per_group, int nranges,
     double* __restrict__ partial) {
   constexpr int KS = PC / 4;       // MFMA steps per chunk = points per lane
   constexpr int STRIDE = PC + 4;   // floats per field row in LDS
@@ -294,8 +300,8 @@ __global__ __launch_bounds__(kBsWaves * 64, JPW <= 8 ? 4 : 2) void k_bs_triple(
   const int grp = blockIdx.x % ngroups, rng = blockIdx.x / ngroups;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, i16 = lane & 15, k4 = lane >> 4;
-  // the jobs are split evenly over the groups and each group's over its waves
-  const int gj0 = (int)((int64_t)njobs * grp / ngroups), gj1 = (int)((int64_t)njobs * (grp + 1) / ngroups);
+  const int gj0 = per_group ? min(njobs, grp * per_group) : (int)((int64_t)njobs * grp / ngroups);
+  const int gj1 = per_group ? min(njobs, gj0 + per_group) : (int)((int64_t)njobs * (grp + 1) / ngroups);
   const int j0 = gj0 + (gj1 - gj0) * wave / kBsWaves;
   const int nj = gj0 + (gj1 - gj0) * (wave + 1) / kBsWaves - j0;  // <= JPW
   double acc[JPW][4];
@@ -445,6 +451,12 @@ hipError_t launch_bs_setup(const Geom& g, const Buffers& b, int mock, int n_dk, 
   return hipGetLastError();
 }
 
+// full groups where equal ones would leave a wave with as many jobs
+static int bs_per_group(const BsPlan& pl) {
+  const int64_t most = pl.ngroups > 0 ? (pl.njobs + pl.ngroups - 1) / pl.ngroups : 0;
+  return most > kBsWaves * (kBsJobsPerWave - 1) ? kBsJobsPerGroup : 0;
+}
+
 template <int PC, int JPW>
 static hipError_t triple_t(const BsPlan& pl, const float2* slab, int n_bins, const int32_t* jobs,
                            double* part, hipStream_t s) {
@@ -457,7 +469,7 @@ static hipError_t triple_t(const BsPlan& pl, const float2* slab, int n_bins, con
   }
   hipLaunchKernelGGL((k_bs_triple<PC, JPW>), dim3((unsigned)(pl.ngroups * pl.nranges)),
                      dim3(kBsWaves * 64), lds, s, slab, pl.npts, pl.Q, n_bins, jobs, (int)pl.njobs,
-                     pl.ngroups, pl.nranges, part);
+                     pl.ngroups, bs_per_group(pl), pl.nranges, part);
   return hipGetLastError();
 }
 

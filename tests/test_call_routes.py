@@ -121,3 +121,26 @@ for n_grid, batch, least in ((64, 1, 8), (128, 1, 64), (256, 1, 64), (64, 8, 64)
         fine = [g for name, g, _ in shapes(n_grid, 4, 1, batch, 1 << 22, n) if "k_sort_fine" in name]
         assert fine[0] >= least, (n_grid, batch, n, fine)
 ''')
+
+
+def test_triple_sums_take_whole_rounds():
+    """At most two workgroups per CU of 256, the groups of jobs equally often."""
+    stub_common.run('''
+import numpy as np
+for n_grid, n_bins, groups in ((160, 48, 1), (180, 56, 2), (256, 84, 3), (320, 100, 5), (360, 110, 6), (400, 128, 8), (480, 150, 13)):
+    a, b, c = np.meshgrid(*[np.arange(1, n_bins + 1, dtype=np.int32)] * 3, indexing="ij")
+    tri = np.ascontiguousarray(np.stack([v[(b <= a) & (c <= b) & (c >= a - b)] for v in (a, b, c)], 1))
+    h = handle(n_grid, 4, 1, 1, 1000)
+    lib.estimator_deposit(h, FAKE, 0, None, 1000)
+    lib.estimator_transform(h)
+    size = lib.estimator_bispectrum_workspace_bytes(h, 1, n_bins, len(tri))
+    ws = np.empty(size + 256, np.uint8)  # not touched but where the job lists go
+    at = (ws.ctypes.data + 255) // 256 * 256
+    stub.stub_reset(-1)
+    lib.estimator_bispectrum(h, 0, 1, n_bins, tri, len(tri), at, size, FAKE, FAKE)
+    grids = {stub.stub_grid(i, 0) for i, name in enumerate(launched()) if "k_bs_triple" in name}
+    assert len(grids) == 1
+    grid = grids.pop()
+    assert grid <= 512 and grid % groups == 0 and grid > 512 - groups, (n_grid, n_bins, grid)
+    lib.estimator_destroy(h)
+''')
