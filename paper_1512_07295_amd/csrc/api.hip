@@ -752,12 +752,11 @@ est_status estimator_graph_launch(est_handle h) {
   return ok();
 }
 
-static Tune tune_from_index(const int* id, int cus) {
+static Tune tune_from_index(const int* id, const Tune& now) {
   static const int vals_cols[2] = {8, 16};
   static const int vals_bins[3] = {256, 0, 2048};  // 0: by occupancy
   static const int vals_dep[2] = {512, 1024};
-  Tune t;
-  t.cus = cus;
+  Tune t = now;
   t.cols_c = vals_cols[id[0]];
   t.bin_blocks = vals_bins[id[1]];
   t.dep_threads = vals_dep[id[2]];
@@ -776,7 +775,7 @@ est_status estimator_set_launch(est_handle h, int32_t choice) {
   id[2] = (choice / 4) % 2;
   id[1] = (choice / 8) % 3;
   id[0] = choice / 24;
-  h->tu = tune_from_index(id, h->tu.cus);
+  h->tu = tune_from_index(id, h->tu);
   return ok();
 }
 
@@ -821,8 +820,7 @@ est_status estimator_autotune(est_handle h, const void* pos, est_dtype dtype, co
     return dev_err(hipEventElapsedTime(ms, e0, e1), "elapsed time");
   };
   int idx[5] = {1, 1, 0, 1, 1};  // start from the defaults
-  const int cus = h->tu.cus;
-  auto make = [&](const int* id) { return tune_from_index(id, cus); };
+  auto make = [&](const int* id) { return tune_from_index(id, h->tu); };
   // the 32-bit deposit format (parameter 3) is not a launch shape: it stays
   // on (it is used only when provably safe, and is then always the faster)
   const int nvals[5] = {2, 3, 2, 1, 2};

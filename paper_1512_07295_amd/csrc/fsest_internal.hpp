@@ -113,6 +113,8 @@ struct Buffers {
   double* mode_partials_k;    // kMaxBinBlocks * kMaxBins
 };
 
+constexpr int kMultiResident = 3;
+
 // Launch shapes chosen per handle (the autotuner changes them).
 struct Tune {
   int cols_c = 16;        // lines per workgroup of the strided FFT passes
@@ -121,6 +123,10 @@ struct Tune {
   int dep_narrow = 1;     // 32-bit fixed point when provably safe (else 64-bit)
   int dep_xcd = 1;        // its consecutive tiles on one XCD (shared L2)
   int cus = 256;          // compute units of the handle's device (set at create)
+  // workgroups per CU of the pair pass in modes 0..2 and of the multi-grid one
+  // from stored spectra and fused (kMultiResident), asked of the runtime once
+  // per handle (0: not yet): they depend on the kernel and its LDS alone
+  mutable int resident[5] = {0, 0, 0, 0, 0};
 };
 
 // Device helper: wrap one float64 coordinate into [0, L) with the fixed

@@ -480,10 +480,13 @@ __global__ void k_adjoint_coef(const double* __restrict__ dldp, int n_bins, cons
 // round and a third at 1024^3, one row group per workgroup for a batch):
 // 1024^3 2.45 -> 2.06 ms, 480^3 0.60 -> 0.49, 64 sets of 128^3 0.38 -> 0.28.
 // tu.bin_blocks > 0: that many (the autotuner's choice).
-static int resident_blocks(const void* kernel, const Geom& g, const Tune& tu, int threads, size_t lds) {
-  int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds) != hipSuccess || per_cu < 1)
+static int resident_blocks(const void* kernel, const Geom& g, const Tune& tu, int which, int threads, size_t lds) {
+  int& per_cu = tu.resident[which];
+  if (per_cu == 0 &&
+      (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds) != hipSuccess || per_cu < 1)) {
+    (void)hipGetLastError();  // one workgroup per CU will do
     per_cu = 1;
+  }
   return (tu.cus * per_cu + g.batch - 1) / g.batch;
 }
 
@@ -493,7 +496,7 @@ static int pair_blocks(const Geom& g, const Tune& tu, int threads, int ppb) {
   const int64_t npairs = (int64_t)g.n * g.n / 2 + 2;
   const int64_t groups = (npairs + ppb - 1) / ppb;
   int64_t nblk = tu.bin_blocks;
-  if (nblk <= 0) nblk = resident_blocks((const void*)k_pairs<L, IL, MODE>, g, tu, threads, 0);
+  if (nblk <= 0) nblk = resident_blocks((const void*)k_pairs<L, IL, MODE>, g, tu, MODE, threads, 0);
   if (nblk > groups) nblk = groups;
   if (nblk > kMaxBinBlocks) nblk = kMaxBinBlocks;
   return (int)nblk;
@@ -688,7 +691,7 @@ static hipError_t multi_pairs_t(const Geom& g, const Buffers& b, const Tune& tu,
     attr_set = true;
   }
   const int64_t npairs = (int64_t)g.n * g.n / 2 + 2;
-  int64_t blocks = resident_blocks((const void*)k_multi_pairs<L, FFT>, g, tu, threads, lds);
+  int64_t blocks = resident_blocks((const void*)k_multi_pairs<L, FFT>, g, tu, kMultiResident + (FFT ? 1 : 0), threads, lds);
   if (blocks > npairs) blocks = npairs;
   if (blocks > kMaxBinBlocks) blocks = kMaxBinBlocks;
   *nblk = (int)blocks;
