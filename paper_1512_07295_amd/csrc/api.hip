@@ -823,7 +823,12 @@ est_status estimator_autotune(est_handle h, const void* pos, est_dtype dtype, co
   auto make = [&](const int* id) { return tune_from_index(id, h->tu); };
   // the 32-bit deposit format (parameter 3) is not a launch shape: it stays
   // on (it is used only when provably safe, and is then always the faster)
-  const int nvals[5] = {2, 3, 2, 1, 2};
+  // and a parameter that no kernel of this call reads is not tried: the lines per
+  // workgroup belong to lengths that are powers of two, the reduction's
+  // workgroups to one or two grids, the rest to the general deposit kernel
+  const bool pow2 = (h->g.n & (h->g.n - 1)) == 0;
+  const bool general = h->cfg.order > 4 || h->g.n <= kTileMax || !walks(h->cfg, n_total);
+  const int nvals[5] = {pow2 ? 2 : 1, h->g.npair == 1 ? 3 : 1, general ? 2 : 1, 1, general ? 2 : 1};
   float best_ms = 1e30f;
   if (st == EST_OK) st = measure(make(idx), &best_ms);
   for (int p = 0; p < 5 && st == EST_OK; ++p) {

@@ -35,3 +35,23 @@ for n_grid in (32, 60):
         assert stub.stub_occupancy_queries() == 0
         lib.estimator_destroy(h)
 ''')
+
+
+def test_autotune_tries_what_the_call_reads():
+    """The stub's times fall from trial to trial, so that every parameter that is
+    tried changes and the others keep their defaults (choice 35)."""
+    stub_common.run('''
+def digits(choice):
+    return choice // 24, choice // 8 % 3, choice // 4 % 2, choice // 2 % 2, choice % 2
+
+# (n_grid, order, interlace, particles): tried lines, reduction, deposit
+for n_grid, order, code, n, tried in ((32, 4, 1, 5000, (1, 1, 0)), (60, 4, 1, 5000, (0, 1, 0)), (32, 4, 2, 5000, (1, 0, 0)),
+                                      (100, 3, 3, 5000, (0, 0, 0)), (32, 5, 1, 5000, (1, 1, 1)), (16, 2, 0, 500, (1, 1, 1)),
+                                      (512, 2, 1, 1 << 20, (1, 1, 1)), (512, 2, 1, 1 << 26, (1, 1, 0))):
+    h = handle(n_grid, order, code, 1, n)
+    got = digits(lib.estimator_autotune(h, FAKE, 0, None, n, 1, 4, 1))
+    default = digits(35)
+    for i, on in ((0, tried[0]), (1, tried[1]), (2, tried[2]), (3, 0), (4, tried[2])):
+        assert (got[i] != default[i]) == bool(on), (n_grid, order, code, n, got)
+    lib.estimator_destroy(h)
+''')
