@@ -65,9 +65,8 @@ typedef enum { EST_F32 = 0, EST_F64 = 1 } est_dtype;
 /* est_config.flags.  Particles are bucket-sorted (4^3-cell buckets) before
  * the deposit.  By default the sort works in two levels without
  * device-scope atomics: per-workgroup histograms over super-buckets of
- * up to 16^3 buckets (the edge is a divisor of N/4, chosen by the particle
- * capacity),
- * then one workgroup per super-bucket.  That workgroup count
+ * up to 16^3 buckets (the edge is a divisor of N/4, chosen from the particles
+ * of the call), then one workgroup per super-bucket.  That workgroup count
  * bounds the second level, so for strongly clustered inputs (a large
  * fraction of all particles inside one super-bucket) this flag selects
  * the single-level counting sort with device-scope atomics instead.  The
@@ -100,7 +99,8 @@ typedef struct {
   int32_t reserved;      /* must be 0                                          */
 } est_config;
 
-/* Bytes of device workspace a handle with this configuration needs.
+/* Bytes of device workspace a handle with this configuration needs.  The
+ * size belongs to this build of the library: ask for it, don't keep it.
  * Host only.  EINVAL for an invalid config, EUNSUPPORTED for an N outside
  * the set above, ENOMEM if the size overflows. */
 est_status estimator_workspace_bytes(const est_config* cfg, size_t* bytes);
@@ -203,13 +203,13 @@ est_status estimator_graph_launch(est_handle h);
 
 /* Pick this handle's launch shapes (strided-FFT lines per workgroup, P(k)
  * reduction workgroups, and of the general deposit kernel, which runs for
- * orders 5 and 6, N <= 16 and low orders on sparse grids, the workgroup size
- * and grouping per XCD) by
- * timing the whole pipeline on the given input `iters` times per candidate,
- * one parameter at a time.  The 32-bit fixed-point deposit stays selected (it runs only where provably safe); estimator_set_launch can
- * force the 64-bit one.  Returns the chosen combination as an index in
- * [0, 48) in *choice.  Results do not depend on the choice beyond rounding.
- * Host-synchronising. */
+ * orders 5 and 6, N <= 16 and sparse grids, the workgroup size and grouping
+ * per XCD) by timing the whole pipeline on the given input `iters` times per
+ * candidate, one parameter at a time, those that no kernel of the call reads
+ * left at their defaults.  The 32-bit fixed-point deposit stays selected (it
+ * runs only where provably safe); estimator_set_launch can force the 64-bit
+ * one.  Returns the chosen combination as an index in [0, 48) in *choice.
+ * Results do not depend on the choice beyond rounding.  Host-synchronising. */
 est_status estimator_autotune(est_handle h, const void* pos, est_dtype dtype,
                               const int64_t* offsets, int64_t n_total,
                               int32_t n_dk, int32_t n_bins, int32_t iters,
@@ -217,8 +217,12 @@ est_status estimator_autotune(est_handle h, const void* pos, est_dtype dtype,
 
 /* Set the launch shapes directly from an index returned by
  * estimator_autotune (e.g. one cached from an earlier run).  EINVAL outside
- * [0, 48).  Until a handle's shapes are set or tuned, the P(k) reduction
- * has as many workgroups as the device holds at once. */
+ * [0, 48).  The index is (((l * 3 + r) * 2 + t) * 2 + f) * 2 + g: lines per
+ * workgroup 8 or 16 (l), P(k) reduction workgroups per set 256, as many as the
+ * device holds at once, or 2048 (r), general deposit workgroups of 512 or 1024
+ * threads (t), 64-bit deposit or 32-bit where safe (f), its tiles in order or
+ * grouped per XCD (g).  Until a handle's shapes are set or tuned they are those
+ * of index 35, with the general deposit's workgroup size chosen per kernel. */
 est_status estimator_set_launch(est_handle h, int32_t choice);
 
 /* Per-particle masses (the paper takes equal masses for simplicity,

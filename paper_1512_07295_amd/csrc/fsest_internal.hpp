@@ -47,9 +47,9 @@ struct Geom {
   int npair;      // complex grids (slabs) per set: max(1, ng / 2); slab = set * npair + q
   int batch;
   int nb;         // buckets per axis = N / kBucket
-  bool walk;      // the deposit walks columns of tiles (deposit_walk.hip)
+  bool walk;      // the call's deposit walks columns of tiles (deposit_walk.hip)
   int tile;       // deposit tile edge
-  int fb;         // buckets per super-bucket edge: min(kFineMax, nb)
+  int fb;         // the call's buckets per super-bucket edge: a divisor of nb, at most kFineMax
   uint32_t fb_mul;  // floor(2^32 / fb) + 1 (fb >= 2): x / fb = umulhi(x, fb_mul) for x < 2^16
   int sa;         // super-buckets per axis: nb / fb
   int nsup;       // batch * sa^3 (two-level sort when <= kMaxSuper)
@@ -89,9 +89,9 @@ struct Buffers {
   uint32_t* hsup;          // sort_blocks(n) x nsup block-major histograms / offsets,
                            // then the nsup + 1 super-bucket starts and the nsup totals
   uint32_t* scan_tmp;      // scan block sums (atomic sort)
-  uint32_t* stats;         // [0] largest bucket count of the last sort, [1] tile counter,
-                           // [4] largest mass (float bits), [5] nonzero if a mass is
-                           // negative or not finite
+  uint32_t* stats;         // [0] largest bucket count of the last sort, [1] the deposit's unit
+                           // counter, [3] the bucket pass's super-bucket counter, [4] largest mass
+                           // (float bits), [5] nonzero if a mass is negative or not finite
   float2* tw_n;            // exp(-2 pi i n / N)
   float2* tw_nz;           // exp(-2 pi i n / nz)
   float* inv_w2;           // 1 / W_1D(m(i))^2 for FFT index i (N entries)
