@@ -44,7 +44,8 @@ def run(body):
         so = os.path.join(tmp, "hip_stub.so")
         subprocess.run(["gcc", "-O1", "-fPIC", "-shared", "-o", so, os.path.join(HERE, "hip_stub.c")], check=True)
         # no device for the parts of torch that see the real runtime
-        env = dict(os.environ, LD_PRELOAD=so, HIP_VISIBLE_DEVICES="-1")
+        preload = " ".join(filter(None, [so, os.environ.get("LD_PRELOAD")]))
+        env = dict(os.environ, LD_PRELOAD=preload, HIP_VISIBLE_DEVICES="-1")
         out = subprocess.run([sys.executable, "-c", PROLOGUE + body], env=env, capture_output=True, text=True,
                              timeout=600)
     assert out.returncode == 0, out.stderr[-4000:]
