@@ -217,11 +217,12 @@ bool walks(const est_config& c, int64_t n) {
 // mass is a second scattered write, of 4 bytes, in both passes (256^3, one
 // particle per cell: in random order 1.74 ms with 4K particles per super-bucket,
 // 1.28 with 16K, in lattice order 0.64 and 0.50; 512^3, one in eight cells,
-// 1.85 and 1.45).  At small sizes up to 512 super-buckets, so that the bucket
-// pass has workgroups: below n / 512 (32768 particles on 64^3: sort 61 us with
-// two super-buckets, 25 with 64), or one per 512 buckets, whose offsets the
-// bucket pass writes (4096 particles on 128^3: 25 us with 8 super-buckets, 23 with
-// 64).  If none qualifies, the largest.  The count never falls as n grows.
+// 1.85 and 1.45), unless the divisors of nb then leave more than 128K (300^3, one
+// per cell: 2.72 ms with 216K, 2.30 with 8K).  At small sizes up to 512
+// super-buckets, so that the bucket pass has workgroups: below n / 512 (32768
+// particles on 64^3: sort 61 us with two super-buckets, 25 with 64), or one per
+// 512 buckets, whose offsets the bucket pass writes (4096 particles on 128^3:
+// 25 us with 8 super-buckets, 23 with 64).  If none qualifies, the largest.  The count never falls as n grows.
 int super_edge(const est_config& c, int64_t n, bool masses, int least) {
   const int nb = c.n_grid / kBucket;
   const int64_t buckets = (int64_t)c.batch * nb * nb * nb;
@@ -233,11 +234,16 @@ int super_edge(const est_config& c, int64_t n, bool masses, int least) {
   if (target < 1) target = 1;
   if (target > kMaxSuper) target = kMaxSuper;
   int largest = 0;
+  int64_t finer = 0;  // the count of the divisor before
   for (int d = 1; d <= kFineMax && d <= nb; ++d) {
     if (nb % d != 0 || (d < least && d != nb)) continue;
+    const int64_t sa = nb / d, count = c.batch * sa * sa * sa;
+    if (count <= target) {
+      if (masses && finer > 0 && finer <= n / 4096 && finer <= kMaxSuper && n / count > 131072) return largest;
+      return d;
+    }
     largest = d;
-    const int64_t sa = nb / d;
-    if (c.batch * sa * sa * sa <= target) return d;
+    finer = count;
   }
   return largest;
 }

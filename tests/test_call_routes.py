@@ -106,7 +106,8 @@ def test_masses_take_larger_super_buckets():
     """(particles, super-buckets without and with masses): 4K and 16K particles
     each, 64 super-buckets per workgroup of the column scan."""
     stub_common.run(SHAPES + '''
-for n_grid, n, plain, masses in ((256, 1 << 24, 4096, 512), (512, 1 << 24, 4096, 512), (480, 360 ** 3, 8000, 1728), (256, 1 << 20, 512, 512)):
+for n_grid, n, plain, masses in ((256, 1 << 24, 4096, 512), (512, 1 << 24, 4096, 512), (480, 360 ** 3, 8000, 1728), (256, 1 << 20, 512, 512),
+                                  (300, 300 ** 3, 3375, 3375), (300, 15 << 20, 3375, 125)):
     for weights, count in ((False, plain), (True, masses)):
         scan = [g for name, g, _ in shapes(n_grid, 4, 1, 1, n, n, weights) if "k_sup_colscan" in name]
         assert scan == [-(-count // 64)], (n_grid, n, weights, scan)
