@@ -39,7 +39,7 @@ MEASURED_TRAFFIC = {
                     "paper_1512_07295_amd/csrc/deposit.hpp",
                     "paper_1512_07295_amd/csrc/particles.hpp",
                     "paper_1512_07295_amd/csrc/fsest_internal.hpp"],
-        "sha256_16": "d1f530e9ff931b0a",
+        "sha256_16": "f2bf5afc2fc226cf",
         "workload": "pcs_il_n1024_za512",
         "read_bytes": 2 * 3013564 * 1024,
         "write_bytes": 10427721 * 1024,

@@ -1,7 +1,7 @@
 // Mass assignment of orders 1..4 on grids larger than a tile (every N > 16):
 // workgroups walk columns of 16 x 16 x 8-cell tiles in z.  Orders 5 and 6,
-// grids of one tile and the 32-bit format of low orders on sparse grids take
-// the general kernel of deposit.hip.
+// grids of one tile and the 32-bit format on sparse grids take the general
+// kernel of deposit.hip.
 //
 // What bounds it (gfx950): LDS integer atomics and VALU together.  A 32-bit
 // LDS atomic takes at least 4 cycles per wave instruction and CU (16 active
